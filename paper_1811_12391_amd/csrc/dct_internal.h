@@ -300,7 +300,7 @@ struct TransArgs {
     int nblk;
     void *phi_all;            // T [B][G][Nm][C]
     void *ext;                // T [B][Nm][C]
-    void *Qc;                 // T [2][B][Nm][C]
+    void *Qc;                 // T [2][B][Nm][C]: takes the new group's first source, or null
     RhsState *state;
     double *bal;              // [B][G][3]
     int *n_unfinished;
@@ -500,15 +500,16 @@ hipError_t launch_sigc(const Geo &g, const uint8_t *mat, const double *rho, cons
                        void *sigc, int is_f64, hipStream_t s);
 // sigma_t of every group in the chain layout of period K nx (K copies)
 hipError_t launch_sigch(const Geo &g, const void *sigc, int G, int K, void *sigch, int is_f64, hipStream_t s);
+// workgroups of a transition: 16 x 16 voxels of a layer each
+inline long voxel_blocks(int nx, int ny, int nz) { return (long)((nx + 15) / 16) * ((ny + 15) / 16) * nz; }
 hipError_t launch_transition(const TransArgs &a, int is_f64, hipStream_t s);
 hipError_t launch_combine(const CombArgs &a, int is_f64, hipStream_t s);
-hipError_t launch_qinit(const CombArgs &a, int is_f64, hipStream_t s);
 // Anderson acceleration: dot products and mixing coefficients, then the mixed
 // iterate phi_00 (and the moment-0 source in both class layouts)
 hipError_t launch_aa(const AAArgs &a, int is_f64, hipStream_t s);
 // D map + combine + M map of one iteration in one kernel (forward FP64 / FP32 solves)
 // first = 1: only the sources at the first iteration of a group, whose q the
-// kernel forms from ext alone (the work of k_qinit and the M map)
+// kernel forms from ext alone (its first source and the M map)
 // max_wg > 0: at most that many (persistent) workgroups, each taking several
 // slabs in turn
 hipError_t launch_dcm(const CombArgs &a, const MapArgs &m, int is_f64, hipStream_t s, int first = 0,

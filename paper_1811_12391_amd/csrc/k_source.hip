@@ -62,6 +62,43 @@ __device__ inline double block_max(double v, double *red)
     return t;
 }
 
+// A workgroup of the transitions takes 16 x 16 voxels of one layer, a wave 16 in
+// x by 4 in y: its accesses in the natural layout are 4 whole lines or halves,
+// and in a class layout, where the 16 y of a row lie side by side, 19 lines
+// instead of the 64 of a wave along x.
+struct VoxelOf {
+    int i, j, k;
+    long v;
+    bool in;
+};
+__device__ inline VoxelOf voxel_of_block(const Geo &geo)
+{
+    const int nti = (geo.nx + 15) >> 4, ntj = (geo.ny + 15) >> 4;
+    const int kj = (int)blockIdx.x / nti, ti = (int)blockIdx.x - kj * nti, k = kj / ntj;
+    const int i = 16 * ti + ((int)threadIdx.x & 15), j = 16 * (kj - k * ntj) + ((int)threadIdx.x >> 4);
+    return VoxelOf{i, j, k, i + (long)geo.nx * (j + (long)geo.ny * k), i < geo.nx && j < geo.ny};
+}
+
+// Offsets of one voxel in the two class layouts, and a first source laid there
+// (one right-hand side's part of Qc, class B half a class on).  The transitions
+// store it themselves: a kernel of its own, through an LDS tile, wrote whole
+// lines once a group but cost every iteration of the group a launch that found
+// nothing to do (64 x 64 x 16, S8 P3, 19 groups, 165 iterations: 16.35 ms a
+// solve with it, 16.11 without, 16.03 once the transitions took 16 x 16 voxels).
+struct ClassPos {
+    long a, b;
+};
+__device__ inline ClassPos class_pos(const Geo &geo, int i, int j, int k)
+{
+    return ClassPos{cls_pos(0, i, j, k, geo.nx, geo.ny), cls_pos(1, i, j, k, geo.nx, geo.ny)};
+}
+template <typename T>
+__device__ inline void lay_source(T *Q, long half, ClassPos p, T x)
+{
+    Q[p.a] = x;
+    Q[half + p.b] = x;
+}
+
 // LT: the P_N order as a compile-time constant, so that the harmonics of a
 // voxel's source direction stay in registers
 template <typename T, int LT>
@@ -75,8 +112,9 @@ __global__ __launch_bounds__(256) void k_transition(TransArgs a)
     const int g = st->g;
     const Geo &geo = a.geo;
     const long C = geo.C;
-    const long v = (long)blockIdx.x * 256 + threadIdx.x;
-    const bool inb = v < C;
+    const VoxelOf vx = voxel_of_block(geo);
+    const long v = vx.v;
+    const bool inb = vx.in;
     const int G = a.G, L = LT, Nm = NM;
     double Rp = 0.0, Pp = 0.0;
     T *phi_all = (T *)a.phi_all;
@@ -91,10 +129,10 @@ __global__ __launch_bounds__(256) void k_transition(TransArgs a)
             Rp = (sig - s0) * (double)phi_all[(((long)b * G + gp) * Nm) * C + v];
         }
         if (g < G) {
-            const int i = (int)(v % geo.nx);
-            const int j = (int)((v / geo.nx) % geo.ny);
-            const int k = (int)(v / ((long)geo.nx * geo.ny));
-            T *ext = (T *)a.ext + (long)b * Nm * C;   // the first source of the group (k_qinit lays it out for the sweep)
+            const int i = vx.i, j = vx.j, k = vx.k;
+            T *ext = (T *)a.ext + (long)b * Nm * C;
+            T *Q = a.Qc ? (T *)a.Qc + (long)b * Nm * C : nullptr;
+            const ClassPos qp = class_pos(geo, i, j, k);
             // every moment accumulates in the same order as before: first-
             // collision terms g' = 0..g (per superposed source, each source's
             // sum added in turn), the volume source, then downscatter
@@ -142,6 +180,16 @@ __global__ __launch_bounds__(256) void k_transition(TransArgs a)
             for (int lm = 0; lm < NM; ++lm) {
                 T et = (T)e[lm];
                 ext[(long)lm * C + v] = et;
+                if (Q) {
+                    // the group's first source, laid out for the M map: ext, and in a
+                    // warm start the within-group scatter of the moments it begins
+                    // from, as k_combine forms the later ones
+                    T q0 = et;
+                    if (a.warm)
+                        q0 = (T)((double)et + rho * sm[((long)l_of(lm) * G + g) * G + g] *
+                                                  (double)phi_all[(((long)b * G + g) * Nm + lm) * C + v]);
+                    lay_source(Q + (long)lm * C, (long)a.B * Nm * C, qp, q0);
+                }
                 if (!a.warm) phi_all[(((long)b * G + g) * Nm + lm) * C + v] = (T)0;
                 if (lm == 0 && a.aa_phik)
                     a.aa_phik[(long)b * C + v] = a.warm ? (double)phi_all[(((long)b * G + g) * Nm) * C + v] : 0.0;
@@ -226,13 +274,12 @@ __global__ __launch_bounds__(256) void k_adj_transition(AdjTransArgs a)
     const int G = a.G, L = LT, Nm = NM, N = a.N;
     const Geo &geo = a.geo;
     const long C = geo.C;
-    const long v = (long)blockIdx.x * 256 + threadIdx.x;
-    if (v < C) {
+    const VoxelOf vx = voxel_of_block(geo);
+    const long v = vx.v;
+    if (vx.in) {
         const int m = a.mat[v];
         const double rho = a.rho[v];
-        const int i = (int)(v % geo.nx);
-        const int j = (int)((v / geo.nx) % geo.ny);
-        const int k = (int)(v / ((long)geo.nx * geo.ny));
+        const int i = vx.i, j = vx.j, k = vx.k;
         const double *p = a.pos + 3 * b;
         double d0 = geo.org[0] + (i + 0.5) * geo.dx - p[0];
         double d1 = geo.org[1] + (j + 0.5) * geo.dy - p[1];
@@ -249,49 +296,114 @@ __global__ __launch_bounds__(256) void k_adj_transition(AdjTransArgs a)
             const T *lc = (const T *)a.lamc + (long)b * N * C;
             const long pos0 = cls_pos(0, i, j, k, geo.nx, geo.ny), pos1 = cls_pos(1, i, j, k, geo.nx, geo.ny);
             double sbar = 0.0;
-            for (int n = 0; n < N; ++n) {
+            int n = 0;
+            for (; n + 8 <= N; n += 8) {
+                T x[8], y[8];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    const long pp = (long)(n + q) * C +
+                                    (dir_class(a.dirs[3 * (n + q)], a.dirs[3 * (n + q) + 1]) == 0 ? pos0 : pos1);
+                    x[q] = lc[pp];
+                    y[q] = pk[pp];
+                }
+#pragma unroll
+                for (int q = 0; q < 8; ++q) sbar -= (double)x[q] * (double)y[q];
+            }
+            for (; n < N; ++n) {
                 const long pp = dir_class(a.dirs[3 * n], a.dirs[3 * n + 1]) == 0 ? pos0 : pos1;
                 sbar -= (double)lc[(long)n * C + pp] * (double)pk[(long)n * C + pp];
             }
             double drv = a.st[m * G + gp] * sbar;
+            // HBM-bound.  Group by group with the moments inside: every moment's
+            // loads of a group are in flight together and its uncollided weight
+            // is read and written once, not once a moment (each sum keeps its
+            // order: scattered flux of g2 < gp, then the uncollided terms).  With
+            // the 16 x 16 voxel blocks and the source laid out here, a gradient
+            // at 64 x 64 x 16, S8 P3, 19 groups went from 35.3 to 32.7 ms.
             const T *lamg = lam_all + ((long)b * G + gp) * Nm * C;
+            const double *sm = a.ss + (long)m * (L + 1) * G * G;
+            double lv[NM], dq[NM];
 #pragma unroll
             for (int lm = 0; lm < NM; ++lm) {
-                const int l = l_of(lm);
-                const double *sl = a.ss + ((long)m * (L + 1) + l) * G * G;
-                const double lv = (double)lamg[(long)lm * C + v];
-                double dq = sl[gp * G + gp] * (double)phi_all[(((long)b * G + gp) * Nm + lm) * C + v];
-                for (int g2 = 0; g2 < gp; ++g2) {
-                    double s = sl[g2 * G + gp];
-                    if (s != 0.0) dq += s * (double)phi_all[(((long)b * G + g2) * Nm + lm) * C + v];
-                }
-                for (int g2 = 0; g2 <= gp; ++g2) {
-                    double s = sl[g2 * G + gp];
-                    if (s != 0.0) {
-                        const double pu = a.phi_u[((long)b * G + g2) * C + v];
-                        dq += s * pu * Y[lm];
-                        a.pbu[((long)b * G + g2) * C + v] += rho * s * Y[lm] * lv;
-                    }
-                }
-                drv += lv * dq;
+                lv[lm] = (double)lamg[(long)lm * C + v];
+                dq[lm] = sm[((long)l_of(lm) * G + gp) * G + gp] * (double)phi_all[(((long)b * G + gp) * Nm + lm) * C + v];
             }
+            for (int g2 = 0; g2 < gp; ++g2) {
+                double sl[LT + 1];
+                bool any = false;
+#pragma unroll
+                for (int l = 0; l <= LT; ++l) {
+                    sl[l] = sm[((long)l * G + g2) * G + gp];
+                    any = any || sl[l] != 0.0;
+                }
+                if (!any) continue;
+                const T *ph = phi_all + ((long)b * G + g2) * Nm * C + v;
+                T f[NM];
+#pragma unroll
+                for (int lm = 0; lm < NM; ++lm) f[lm] = ph[(long)lm * C];
+#pragma unroll
+                for (int lm = 0; lm < NM; ++lm) {
+                    const double s = sl[l_of(lm)], t = dq[lm] + s * (double)f[lm];
+                    dq[lm] = s != 0.0 ? t : dq[lm];
+                }
+            }
+            for (int g2 = 0; g2 <= gp; ++g2) {
+                double sl[LT + 1];
+                bool any = false;
+#pragma unroll
+                for (int l = 0; l <= LT; ++l) {
+                    sl[l] = sm[((long)l * G + g2) * G + gp];
+                    any = any || sl[l] != 0.0;
+                }
+                if (!any) continue;
+                const double pu = a.phi_u[((long)b * G + g2) * C + v];
+                double pb = a.pbu[((long)b * G + g2) * C + v];
+#pragma unroll
+                for (int lm = 0; lm < NM; ++lm) {
+                    const double s = sl[l_of(lm)], t = dq[lm] + s * pu * Y[lm], u = pb + rho * s * Y[lm] * lv[lm];
+                    dq[lm] = s != 0.0 ? t : dq[lm];
+                    pb = s != 0.0 ? u : pb;
+                }
+                a.pbu[((long)b * G + g2) * C + v] = pb;
+            }
+#pragma unroll
+            for (int lm = 0; lm < NM; ++lm) drv += lv[lm] * dq[lm];
             a.drho[(long)b * C + v] += drv;
         }
         if (gs < G) {
             const int g = G - 1 - gs;              // the group to set up
             T *pb = (T *)a.phibar + (long)b * Nm * C;
-            // the first adjoint source of the group is phibar (k_qinit lays it out for the sweep)
+            // the first adjoint source of the group is phibar
+            T *Q = (T *)a.Qc + (long)b * Nm * C;
+            const ClassPos qp = class_pos(geo, i, j, k);
+            const double *sm = a.ss + (long)m * (L + 1) * G * G;
+            double e[NM];
+#pragma unroll
+            for (int lm = 0; lm < NM; ++lm) e[lm] = lm == 0 ? a.roi[v] * a.kap[m * G + g] : 0.0;
+            for (int g2 = g + 1; g2 < G; ++g2) {
+                double sl[LT + 1];
+                bool any = false;
+#pragma unroll
+                for (int l = 0; l <= LT; ++l) {
+                    sl[l] = sm[((long)l * G + g) * G + g2];
+                    any = any || sl[l] != 0.0;
+                }
+                if (!any) continue;
+                const T *lp = lam_all + ((long)b * G + g2) * Nm * C + v;
+                T f[NM];
+#pragma unroll
+                for (int lm = 0; lm < NM; ++lm) f[lm] = lp[(long)lm * C];
+#pragma unroll
+                for (int lm = 0; lm < NM; ++lm) {
+                    const double s = sl[l_of(lm)], t = e[lm] + rho * s * (double)f[lm];
+                    e[lm] = s != 0.0 ? t : e[lm];
+                }
+            }
 #pragma unroll
             for (int lm = 0; lm < NM; ++lm) {
-                const int l = l_of(lm);
-                const double *sl = a.ss + ((long)m * (L + 1) + l) * G * G;
-                double e = lm == 0 ? a.roi[v] * a.kap[m * G + g] : 0.0;
-                for (int g2 = g + 1; g2 < G; ++g2) {
-                    double s = sl[g * G + g2];
-                    if (s != 0.0) e += rho * s * (double)lam_all[(((long)b * G + g2) * Nm + lm) * C + v];
-                }
-                const T et = (T)e;
+                const T et = (T)e[lm];
                 pb[(long)lm * C + v] = et;
+                lay_source(Q + (long)lm * C, (long)a.B * Nm * C, qp, et);
                 lam_all[(((long)b * G + g) * Nm + lm) * C + v] = (T)0;
             }
         }
@@ -323,7 +435,7 @@ __global__ __launch_bounds__(256) void k_adj_transition(AdjTransArgs a)
 hipError_t launch_adj_transition(const AdjTransArgs &a, int is_f64, hipStream_t s)
 {
     if (a.L < 0 || a.L > DCT_MAXL) return hipErrorInvalidValue;
-    dim3 grid((unsigned)((a.geo.C + 255) / 256), a.B);
+    dim3 grid((unsigned)voxel_blocks(a.geo.nx, a.geo.ny, a.geo.nz), a.B);
     if (is_f64) DCT_BY_ORDER(k_adj_transition, double, a.L, grid, dim3(256), 0, s, a);
     else DCT_BY_ORDER(k_adj_transition, float, a.L, grid, dim3(256), 0, s, a);
     return hipGetLastError();
@@ -333,7 +445,7 @@ hipError_t launch_transition(const TransArgs &a, int is_f64, hipStream_t s)
 {
     const int nb = a.nb > 0 ? a.nb : a.B;
     if (a.b0 < 0 || a.b0 + nb > a.B) return hipErrorInvalidValue;
-    dim3 grid((unsigned)((a.geo.C + 255) / 256), nb);
+    dim3 grid((unsigned)voxel_blocks(a.geo.nx, a.geo.ny, a.geo.nz), nb);
     if (a.L < 0 || a.L > DCT_MAXL) return hipErrorInvalidValue;
     if (is_f64) DCT_BY_ORDER(k_transition, double, a.L, grid, dim3(256), 0, s, a);
     else DCT_BY_ORDER(k_transition, float, a.L, grid, dim3(256), 0, s, a);
@@ -1093,7 +1205,7 @@ __global__ __launch_bounds__(256) void k_aa_dots(AAArgs a)
 // k_aa_mix: the mixed iterate phi_{k+1,00} (stored as the iterate of the next
 // sweep and over moment 0 of the group's moments, against which k_combine
 // measures the next change) and its moment-0 source ext_00 + rho s_0 phi in
-// both class layouts, through the slab tile of k_qinit.
+// both class layouts, through a slab tile.
 template <typename T>
 __global__ __launch_bounds__(256) void k_aa_mix(AAArgs a)
 {
@@ -1161,70 +1273,6 @@ hipError_t launch_aa(const AAArgs &a, int is_f64, hipStream_t s)
         hipLaunchKernelGGL(k_aa_dots<float>, gd, dim3(256), 0, s, a);
         hipLaunchKernelGGL(k_aa_mix<float>, gm, dim3(256), shm, s, a);
     }
-    return hipGetLastError();
-}
-
-// First within-group source of a group (phi = 0, so Q = ext): after a group
-// transition (iteration count 0, nothing pending) copy ext from the natural
-// layout into both class layouts through an LDS slab tile, as k_combine does
-// for the later iterations.  Every other iteration it returns at once.
-template <typename T>
-__global__ __launch_bounds__(256) void k_qinit(CombArgs a)
-{
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-    T *tile = (T *)smem_raw;
-    const int b = blockIdx.y;
-    const RhsState *st = a.state + b;
-    if (st->finished || st->pending || st->it != 0) return;
-    const int nx = a.geo.nx, ny = a.geo.ny;
-    const long C = a.geo.C;
-    const int Nm = a.Nm;
-    const int nslj = (ny + 15) >> 4;
-    const int k = blockIdx.x / nslj;
-    const int j0 = (blockIdx.x % nslj) * 16;
-    const int lm = blockIdx.z;
-    const int pitch = (nx | 1) + 1;
-    const int tile_n = 16 * nx;
-    const T *ext = (const T *)a.ext + ((long)b * Nm + lm) * C;
-    T *QA = (T *)a.Qc + ((long)b * Nm + lm) * C;
-    T *QB = (T *)a.Qc + (((long)a.B + b) * Nm + lm) * C;
-    // warm start: the group starts from the moments phi already stored, so its
-    // first source is ext + sigma_s^{gg} phi, as k_combine forms the later ones
-    const int g = eff_group(st->g, a.G, a.reverse);
-    const T *ph = (const T *)a.phi_all + (((long)b * a.G + g) * Nm + lm) * C;
-    const int L = a.L, l = l_of(lm);
-    for (int idx = threadIdx.x; idx < tile_n; idx += 256) {
-        const int jn = idx / nx, in = idx - jn * nx, jj = j0 + jn;
-        if (jj < ny) {
-            const long v = in + (long)nx * (jj + (long)ny * k);
-            if (a.warm) {
-                const int mm = a.mat[v];
-                const double sc = a.rho[v] * a.ss[(((long)mm * (L + 1) + l) * a.G + g) * a.G + g];
-                tile[jn * pitch + in] = (T)((double)ext[v] + sc * (double)ph[v]);
-            } else {
-                tile[jn * pitch + in] = ext[v];
-            }
-        }
-    }
-    __syncthreads();
-    for (int idx = threadIdx.x; idx < tile_n; idx += 256) {
-        const int r = idx >> 4, jl = idx & 15, j = j0 + jl;
-        if (j < ny) {
-            const int jm = j % nx;
-            const long p = ((long)k * nx + r) * ny + j;
-            QA[p] = tile[jl * pitch + rot_row(1, r, jm, nx)];
-            QB[p] = tile[jl * pitch + rot_row(0, r, jm, nx)];
-        }
-    }
-}
-
-hipError_t launch_qinit(const CombArgs &a, int is_f64, hipStream_t s)
-{
-    const int nslj = (a.geo.ny + 15) >> 4;
-    dim3 grid((unsigned)(a.geo.nz * nslj), a.B, a.Nm);
-    size_t shm = (size_t)16 * ((a.geo.nx | 1) + 1) * (is_f64 ? 8 : 4);
-    if (is_f64) hipLaunchKernelGGL(k_qinit<double>, grid, dim3(256), shm, s, a);
-    else hipLaunchKernelGGL(k_qinit<float>, grid, dim3(256), shm, s, a);
     return hipGetLastError();
 }
 

@@ -782,7 +782,7 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
     void *d_ccnt;
     HC(dbuf(ctx, "ccnt", (size_t)B * DCT_MAXNM * 128, &d_ccnt));
     // transition kernels: completion sub-counters and per-workgroup balance sums
-    const int tr_blocks = (int)((C + 255) / 256), tr_nsub = (tr_blocks + 31) / 32;
+    const int tr_blocks = (int)voxel_blocks(nx, ny, nz), tr_nsub = (tr_blocks + 31) / 32;
     void *d_tsub, *d_pbal;
     HC(dbuf(ctx, "tsub", (size_t)B * tr_nsub * 128, &d_tsub));
     HC(dbuf(ctx, "pbal", (size_t)B * tr_blocks * 16, &d_pbal));
@@ -1203,7 +1203,6 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
                 // the M map fills q; the candidate sweeps below all compute
                 // that same first sweep
                 HC(launch_transition(tr, is64, s));
-                HC(launch_qinit(cb, is64, s));
                 HC(launch_mmap(ma, mode, s));
                 while (ctx->evpool.size() < 2) {
                     hipEvent_t ev;
@@ -1369,6 +1368,7 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
         SweepArgs swh = sw;
         trh.b0 = cbh.b0 = swh.b0 = b0;
         trh.nb = cbh.nb = swh.nb = nb;
+        if (fused) trh.Qc = nullptr;   // the fused kernel's first form lays ext out itself
         if (swh.rhsK > 1 && nb != B) swh.rhsK = std::max(2, std::min(DCT_MAXRC, (nb + rc_nch - 1) / rc_nch));
         hipError_t e = launch_transition(trh, is64, es);
         if (e != hipSuccess) return e;
@@ -1376,7 +1376,6 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
             // first iteration of a group: q from ext in one pass over the slabs
             if ((e = launch_dcm(cbh, ma, is64, es, 1, dcm_wg)) != hipSuccess) return e;
         } else {
-            if ((e = launch_qinit(cb, is64, es)) != hipSuccess) return e;
             if ((e = launch_mmap(ma, mode, es)) != hipSuccess) return e;
         }
         for (int d = 0; d < (swh.pipe ? 1 : pl.ndiag); ++d) {
@@ -1944,7 +1943,7 @@ static int adjoint_common(dct_ctx *ctx, const double *roi, const dct_opts *opts,
     HC(hipMemsetAsync(d_aeps, 0, (size_t)B * G * 8, s));
     HC(hipMemsetAsync(B_("err"), 0, 4, s));
     HC(hipMemsetAsync(B_("ccnt"), 0, (size_t)B * DCT_MAXNM * 128, s));
-    const int tr_nsub = (int)(((C + 255) / 256 + 31) / 32);
+    const int tr_nsub = (int)((voxel_blocks(nx, ny, nz) + 31) / 32);
     HC(hipMemsetAsync(B_("tsub"), 0, (size_t)B * tr_nsub * 128, s));
     HC(launch_adj_init(C, G, B, (const uint8_t *)B_("mat"), (const double *)B_("kap"), (const double *)d_roi,
                        (double *)d_pbu, s));
@@ -2097,7 +2096,6 @@ static int adjoint_common(dct_ctx *ctx, const double *roi, const dct_opts *opts,
     auto enqueue_set = [&]() -> hipError_t {
         hipError_t e = launch_adj_transition(at, is64, s);
         if (e != hipSuccess) return e;
-        if ((e = launch_qinit(cb, is64, s)) != hipSuccess) return e;
         if ((e = launch_mmap(ma, mode, s)) != hipSuccess) return e;
         for (int d = 0; d < (sw.pipe ? 1 : pl.ndiag); ++d) {
             sw.diag = d;
