@@ -488,7 +488,7 @@ PROFILE_EVERY = 4
 # (about 10-20 s of host time)
 CPU_SOURCES = {"c4": 6}
 CPU_SOURCES_1T = {"c4": 1}   # about 25 s of one core
-COUPLINGS = {1: "lds_counters", 2: "barrier", 3: "pipelined_blocks", 4: "layered_waves_4", 5: "layered_waves_2",
+COUPLINGS = {1: "lds_counters", 2: "barrier", 3: "pipelined_blocks", 4: "tile_waves", 5: "layered_waves_2",
              6: "chained_directions_1", 7: "chained_directions_2", 8: "chained_directions_4",
              9: "chained_sources_2", 10: "chained_sources_1"}
 FUSE = {"auto": 0, "on": 1, "off": -1}

@@ -85,14 +85,19 @@ typedef struct dct_opts {
                                  a workgroup, 2 = one barrier per step, 3 = as 2 with all
                                  blocks of a sweep in one launch, handing block faces over
                                  as they are produced (needs >= 2 blocks of >= 2 z layers,
-                                 otherwise runs as 1), 4 / 5 = layered waves: every wave
-                                 sweeps 4 / 2 z layers as a skewed pipeline in registers,
+                                 otherwise runs as 1), 4 = tile waves: every wave sweeps tiles
+                                 of 4 z layers x 16 y rows, one barrier per 4 steps (needs
+                                 ny <= 64, nz <= 16, sweep_bk >= nz, no test_inflow; otherwise
+                                 runs as 2), 5 = layered waves: every wave
+                                 sweeps 2 z layers as a skewed pipeline in registers,
                                  one barrier per step (needs one block: ny <= 64, nz <= 16,
                                  sweep_bk >= nz; otherwise runs as 2; the transposed sweeps
                                  of dct_adjoint then use 2); 6 / 7 / 8 = chained directions
                                  (sweep_chain) with 1 / 2 / 4 z layers per wave; 9 / 10 =
                                  chained right-hand sides (sweep_rhs_chain) with 2 / 1 z
-                                 layers per wave; 0 = tuned or 1 */
+                                 layers per wave; 0 = tuned, or (with sweep_bk and sweep_chain
+                                 free too) tile waves on any grid of up to 64 layers, coupling
+                                 2 for few directions on a grid of one block, else 1 */
     int superpose;            /* sources per right-hand side S (0 or 1: one each).  With
                                  S > 1 the B sources of dct_set_source form B / S right-hand
                                  sides of S consecutive sources; each is solved once with
@@ -158,7 +163,7 @@ typedef struct dct_opts {
                                  on two streams, so that one half's sweep overlaps the other
                                  half's fused map kernel (the halves are independent; results
                                  are those of one stream bit for bit).  Needs the fused maps,
-                                 graph off and layered waves (coupling 4 / 5, B >= 2) or
+                                 graph off and tile or layered waves (coupling 4 / 5, B >= 2) or
                                  chained sources (9 / 10, B >= 4: a half's launch keeps the
                                  ceil(B / R) chains per direction of one stream, with
                                  ceil(B_half / ceil(B / R)) sources each, at least 2);
@@ -179,7 +184,7 @@ typedef struct dct_stats {
     int iteration_sets;       /* iteration launch sets enqueued (>= max over RHS of iterations) */
     int sweep_bk;             /* sweep schedule that ran: z layers per workgroup */
     int sweep_sync;           /* and coupling (1 LDS counters, 2 barriers, 3 pipelined blocks,
-                                 4 / 5 layered waves of 4 / 2 z layers, 6 / 7 / 8 chained
+                                 4 tile waves, 5 layered waves of 2 z layers, 6 / 7 / 8 chained
                                  directions with 1 / 2 / 4 z layers per wave, 9 / 10 chained
                                  right-hand sides with 2 / 1 z layers per wave) */
     double tune_ms;           /* device time spent timing candidate schedules in this call */

@@ -12,10 +12,17 @@
 // consecutive y indices of one z layer and walks x; at step t lane j handles
 // the cell with i' + j' = const (primed = reflected into the octant's sweep
 // direction).  Two layouts cover the eight octants:
-//   class A (Ox*Oy > 0): pos = (k*nx + (i + j) mod nx) * ny + j
-//   class B (Ox*Oy < 0): pos = (k*nx + (i - j) mod nx) * ny + j
-// In both, the cells of one wave step share the row (k, r) and differ only in
-// j, so the 64 lanes read 64 consecutive elements (descending for Oy < 0).
+// r = (i + j) mod nx in class A (Ox*Oy > 0), (i - j) mod nx in class B
+// (Ox*Oy < 0), and the rows of 16 consecutive y are kept together:
+//   pos = k nx ny + 16 J nx + r w + (j mod 16),  J = j / 16, w = min(16, ny - 16 J)
+// In both, the cells of one wave step share the row r and differ only in j and
+// k.  16 lanes along y read 16 consecutive elements (64 bytes in FP32), and
+// the next step's lie right beside them, so the two halves of a 128-byte line
+// are used in consecutive steps; a slab of 16 rows of one layer (all x) is one
+// contiguous run of every direction, which is what the moment maps read.
+// (With the whole y extent in a row, 64 y rows side by side, the sweep that
+// gives a wave 16 rows of 4 layers would use half of every line it fetches,
+// and the two slabs sharing each line had to meet in one L2.)
 // The moment maps read/write these layouts directly; the combine kernel moves
 // between them and the natural layout through LDS, one (k, 16-row) slab at a
 // time (a slab is closed under both rotations).
@@ -41,10 +48,22 @@ __host__ __device__ inline int rot_row(int cls, int i, int jm, int nx)
     return r;
 }
 
+// width of the 16-row tile that holds row j (the last tile may be narrower)
+__host__ __device__ inline int tile_w(int j, int ny)
+{
+    const int rest = ny - (j & ~15);
+    return rest < 16 ? rest : 16;
+}
+
+// element of row r (already rotated), y row j, layer k
+__host__ __device__ inline long row_pos(int r, int j, int k, int nx, int ny)
+{
+    return (long)k * nx * ny + (long)(j & ~15) * nx + r * tile_w(j, ny) + (j & 15);
+}
+
 __host__ __device__ inline long cls_pos(int cls, int i, int j, int k, int nx, int ny)
 {
-    int r = rot_row(cls, i, j % nx, nx);
-    return ((long)k * nx + r) * ny + j;
+    return row_pos(rot_row(cls, i, j % nx, nx), j, k, nx, ny);
 }
 
 // class of a direction: 0 when Ox and Oy have the same sign
@@ -361,8 +380,8 @@ struct MapArgs {
     int first_only;           // M map: only right-hand sides at the first iteration of a group
 };
 
-// Cell of a class-layout position p = (k nx + r) ny + j of class cls, for
-// addressing q / psi in the chain layout (x = i, y = j, z = k).
+// Cell of a class-layout position p (row_pos) of class cls, for addressing
+// q / psi in the chain layout (x = i, y = j, z = k).
 struct CellKJI {
     int k, j, i;
 };
@@ -372,7 +391,8 @@ __device__ inline CellKJI cell_of(const MapArgs &a, int cls, long p)
     const int pi = (int)p;
     const int k = pi / pl;
     const int rem = pi - k * pl;
-    const int r = rem / a.ny, j = rem - r * a.ny;
+    const int j0 = rem / (16 * a.nx) * 16, w = tile_w(j0, a.ny);
+    const int rt = rem - j0 * a.nx, r = rt / w, j = j0 + rt - r * w;
     int i = cls == 0 ? r - j % a.nx : r + j % a.nx;
     if (i < 0) i += a.nx;
     if (i >= a.nx) i -= a.nx;
@@ -428,6 +448,8 @@ struct SweepArgs {
     const void *sigch;        // T [2][G][K C] sigma_t in the chain layout of period K nx
     int b0 = 0;               // the launch covers right-hand sides b0 .. b0 + nb - 1 (layered
     int nb = 0;               // waves and chained sources; 0: all B); B stays the stride of every [B] array
+    int tS = 0;               // > 0: tile waves, this many y streams (k_sweep_t; whole y and z extent
+                              //      in one workgroup, nblk = 1)
     int rhsK;                 // > 1: one direction of up to rhsK unfinished right-hand sides per
                               //      workgroup, swept back to back (k_sweep_rc)
 };
@@ -518,6 +540,8 @@ size_t dcm_lds_bytes(const CombArgs &a, const MapArgs &m, int is_f64);   // Q = 
 hipError_t launch_mmap(const MapArgs &a, int mode, hipStream_t s);   // mode 0 f64, 1 f32, 2 bf16
 hipError_t launch_dmap(const MapArgs &a, int mode, hipStream_t s);
 hipError_t launch_sweep(SweepArgs a, int is_f64, hipStream_t s, unsigned seq);
+// y streams of a tile-wave sweep (SweepArgs::tS), 0 where it does not apply
+int tile_streams(int nx, int ny, int nz, long nwg, int is_f64, int ncu, size_t lds);
 hipError_t launch_dose(const DoseArgs &a, int is_f64, hipStream_t s);
 // sum_v w[v] x[v] (FP64, fixed order) into part[nb], nb = min(1024, ceil(n / 256));
 // part needs nb + 1 entries

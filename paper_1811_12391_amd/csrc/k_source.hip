@@ -569,7 +569,7 @@ __global__ __launch_bounds__(256) void k_combine(CombArgs a)
             const int idx = threadIdx.x + 256 * e;
             const int r = idx >> 4, jl = idx & 15, j = j0 + jl;
             const bool okr = idx < tile_n && j < ny;
-            const unsigned orot = okr ? (unsigned)(((long)k * nx + r) * ny + j) * TS : DCT_OOB;
+            const unsigned orot = okr ? (unsigned)row_pos(r, j, k, nx, ny) * TS : DCT_OOB;
             va[e] = bld<T>(rA, orot);
             vb[e] = bld<T>(rB, orot);
             const int jn = idx / nx, in = idx - jn * nx, jj = j0 + jn;
@@ -619,7 +619,7 @@ __global__ __launch_bounds__(256) void k_combine(CombArgs a)
             const int r = idx >> 4, jl = idx & 15, j = j0 + jl;
             const bool okr = idx < tile_n && j < ny;
             const int jm = okr ? j % nx : 0;
-            const unsigned orot = okr ? (unsigned)(((long)k * nx + r) * ny + j) * TS : DCT_OOB;
+            const unsigned orot = okr ? (unsigned)row_pos(r, j, k, nx, ny) * TS : DCT_OOB;
             const int rr = okr ? r : 0, jr = okr ? jl : 0;
             bst(rQA, orot, tile[jr * pitch + rot_row(1, rr, jm, nx)]);
             bst(rQB, orot, tile[jr * pitch + rot_row(0, rr, jm, nx)]);
@@ -631,7 +631,7 @@ __global__ __launch_bounds__(256) void k_combine(CombArgs a)
             int r = idx >> 4, jl = idx & 15, j = j0 + jl;
             if (j < ny) {
                 int i = rot_row(1, r, j % nx, nx);          // inverse of (i + j) mod nx
-                long p = ((long)k * nx + r) * ny + j;
+                long p = row_pos(r, j, k, nx, ny);
                 tile[jl * pitch + i] = partA[p];
             }
         }
@@ -640,7 +640,7 @@ __global__ __launch_bounds__(256) void k_combine(CombArgs a)
             int r = idx >> 4, jl = idx & 15, j = j0 + jl;
             if (j < ny) {
                 int i = rot_row(0, r, j % nx, nx);          // inverse of (i - j) mod nx
-                long p = ((long)k * nx + r) * ny + j;
+                long p = row_pos(r, j, k, nx, ny);
                 tile[jl * pitch + i] += partB[p];
             }
         }
@@ -669,7 +669,7 @@ __global__ __launch_bounds__(256) void k_combine(CombArgs a)
             int r = idx >> 4, jl = idx & 15, j = j0 + jl;
             if (j < ny) {
                 int jm = j % nx;
-                long p = ((long)k * nx + r) * ny + j;
+                long p = row_pos(r, j, k, nx, ny);
                 QA[p] = tile[jl * pitch + rot_row(1, r, jm, nx)];
                 QB[p] = tile[jl * pitch + rot_row(0, r, jm, nx)];
             }
@@ -770,12 +770,7 @@ __global__ __launch_bounds__(512) void k_dcm(CombArgs a, MapArgs m)
     const bool fast = m.chainK <= 1;
     const int Nc0 = m.Nc[0], Nc1 = m.Nc[1];
     // persistent workgroups (the tables above are loaded once): workgroup h
-    // takes work items h, h + gridDim.x, ...; item -> (right-hand side, slab).
-    // Two slabs 16 rows apart share the 128-byte lines of psi (64 bytes each
-    // per row and direction in FP32), so they are paired on one XCD: the items
-    // of workgroups h and h + 8 in the same round (same XCD, running together)
-    // are slabs j and j + 1 of the same layer
-    const bool pair = (nslj & 1) == 0 && (NW & 15) == 0 && (gridDim.x & 15) == 0;
+    // takes work items h, h + gridDim.x, ...; item -> (right-hand side, slab)
     for (unsigned lin = blockIdx.x; lin < NW; lin += gridDim.x) {
         // the lane indices pass through an opaque zero, so that the per-lane
         // address arithmetic of the item is formed inside the loop instead of
@@ -785,11 +780,7 @@ __global__ __launch_bounds__(512) void k_dcm(CombArgs a, MapArgs m)
         const int tid = (int)threadIdx.x + lz;
         const int l = tid & 63, col = l & 15, kr = l >> 4;
         const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), nwv = blockDim.x >> 6;
-        unsigned W = lin;
-        if (pair) {
-            const unsigned xcd = lin & 7, slot = lin >> 3;
-            W = 2 * ((slot >> 1) * 8 + xcd) + (slot & 1);
-        }
+        const unsigned W = lin;
         const int bl = __builtin_amdgcn_readfirstlane((int)(W / nsl));
         const int slab = __builtin_amdgcn_readfirstlane((int)(W - (unsigned)bl * nsl));
         const int b = a.b0 + bl;
@@ -809,6 +800,8 @@ __global__ __launch_bounds__(512) void k_dcm(CombArgs a, MapArgs m)
         const bool jok = jj < ny;
         const int jc = jok ? jj : ny - 1;
         const int jm = jc % nx;
+        const int jw = tile_w(j0, ny);                            // elements of a row of the slab
+        const int slab0 = k * nx * ny + j0 * nx + (jc - j0);      // this lane's element of row 0 (C < 2^28)
         // ---- 1. D map of each class into the natural tile.  A wave takes two
         // rows at a time and loads the psi operands of its next pair (the first
         // pair of class B after the last of class A) before the matrix-core work
@@ -826,7 +819,7 @@ __global__ __launch_bounds__(512) void k_dcm(CombArgs a, MapArgs m)
     #pragma unroll
                 for (int h = 0; h < 2; ++h) {
                     const int r = min(r0 + h * nwv, nx - 1);
-                    const unsigned p4 = (unsigned)((((long)k * nx + r) * ny + jc) * (long)sizeof(T));
+                    const unsigned p4 = (unsigned)(slab0 + r * jw) * (unsigned)sizeof(T);
     #pragma unroll
                     for (int u = 0; u < KC; ++u) bv[h][u] = bld<T>(rps, o[u] + p4);
                 }
@@ -836,7 +829,7 @@ __global__ __launch_bounds__(512) void k_dcm(CombArgs a, MapArgs m)
     #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const int r = min(r0 + h * nwv, nx - 1);
-                const long p = ((long)k * nx + r) * ny + jc;
+                const long p = slab0 + r * jw;
                 const CellKJI cc{k, jc, c == 0 ? (r - jm + nx) % nx : (r + jm) % nx};
     #pragma unroll
                 for (int u = 0; u < KC; ++u) bv[h][u] = psi[dir_elem(m, c, cd[min(4 * u + kr, Nc - 1)], p, cc)];
@@ -913,7 +906,7 @@ __global__ __launch_bounds__(512) void k_dcm(CombArgs a, MapArgs m)
         const unsigned cst = (unsigned)(C * (long)sizeof(T));
         // first iteration: the source is the group source ext (plus the
         // within-group scatter of the moments a warm start begins from), laid
-        // into the tile as k_qinit lays it out
+        // into the tile as k_transition forms it
         for (int idx = threadIdx.x; first && idx < tile_n; idx += blockDim.x) {
             const int jl = idx / nx, i = idx - jl * nx, jy = j0 + jl;
             if (jy >= ny) continue;
@@ -988,7 +981,7 @@ __global__ __launch_bounds__(512) void k_dcm(CombArgs a, MapArgs m)
                     }
                 for (int r = wv; r < nx; r += nwv) {
                     const int i = c == 0 ? (r - jm + nx) % nx : (r + jm) % nx;
-                    const unsigned p4 = (unsigned)((((long)k * nx + r) * ny + jc) * (long)sizeof(T));
+                    const unsigned p4 = (unsigned)(slab0 + r * jw) * (unsigned)sizeof(T);
                     T bq[4 * NRB];
     #pragma unroll
                     for (int s = 0; s < 4 * NRB; ++s) bq[s] = tile[min(4 * s + kr, Nm - 1) * LMS + col * pitch + i];
@@ -1009,7 +1002,7 @@ __global__ __launch_bounds__(512) void k_dcm(CombArgs a, MapArgs m)
             const int Nc = c == 0 ? Nc0 : Nc1;
             const int *cd = cds + c * N;
             for (int r = wv; r < nx; r += nwv) {
-                const long p = ((long)k * nx + r) * ny + jc;
+                const long p = slab0 + r * jw;
                 const int i = c == 0 ? (r - jm + nx) % nx : (r + jm) % nx;
                 const CellKJI cc{k, jc, i};
                 T bq[4 * NRB];
@@ -1252,7 +1245,7 @@ __global__ __launch_bounds__(256) void k_aa_mix(AAArgs a)
         const int r = idx >> 4, jl = idx & 15, j = j0 + jl;
         if (j < ny) {
             const int jm = j % nx;
-            const long p = ((long)k * nx + r) * ny + j;
+            const long p = row_pos(r, j, k, nx, ny);
             QA[p] = tile[jl * pitch + rot_row(1, r, jm, nx)];
             QB[p] = tile[jl * pitch + rot_row(0, r, jm, nx)];
         }

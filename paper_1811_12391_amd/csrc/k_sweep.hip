@@ -20,6 +20,8 @@
 // a negative outgoing face is set to zero and psi_c recomputed from the cell
 // balance without that face's diamond relation (its inflow then enters with
 // weight c_a / 2), repeating while new negative faces appear.
+#include <algorithm>
+
 #include "dct_internal.h"
 
 namespace dct {
@@ -252,7 +254,9 @@ __global__ __launch_bounds__(1024) void k_sweep(SweepArgs a)
     const int j = valid ? (sy ? jp : ny - 1 - jp) : 0;
     const int k = valid ? (sz ? kp : nz - 1 - kp) : 0;
     const int jm = j % nx;
-    const int rowbase = k * nx * ny + j;                    // element offsets fit in 32 bits (C*8 < 2^31)
+    // this lane's element of row 0 and its row stride (element offsets fit in
+    // 32 bits: C * 8 < 2^31)
+    const int rowbase = (int)row_pos(0, j, k, nx, ny), rw = tile_w(j, ny);
     const rsrc_t rq = mk_rsrc((const T *)a.q + (long)item * C, C * TS);
     const rsrc_t rpsi = mk_rsrc((T *)a.psi + ((long)b * a.psi_bs + (long)g * a.psi_gs + n) * C, C * TS);
     const rsrc_t rmask = mk_rsrc((ADJ || KEEP) && a.mask ? a.mask + (((long)b * a.G + g) * a.N + n) * C : nullptr, C);
@@ -322,17 +326,15 @@ __global__ __launch_bounds__(1024) void k_sweep(SweepArgs a)
         if (MULTI) yr[MULTI ? u : 0] = zr[MULTI ? u : 0] = (T)0;
         if (ADJ) fr[ADJ ? u : 0] = 0;
     }
-    // Element offsets: one rotated row (ny elements) per x step, wrapping
-    // inside the (k, rotated row) plane.  Lane l reaches x index t - l - w at
+    // Element offsets: one rotated row (rw elements) per x step, wrapping
+    // inside the layer's tile.  Lane l reaches x index t - l - w at
     // step t and the rotation adds (or subtracts) its row j = j0 +- l, so the
     // rotated row of step t is the same for every lane of a wave: the row
-    // part of the offset is a wave-uniform scalar (sre, for the prefetched
-    // step), the lane part a constant (rowbase).  The offsets a prefetch used
+    // index is a wave-uniform scalar (sre, for the prefetched step), the lane
+    // part of the offset a constant (rowbase).  The offsets a prefetch used
     // are kept and reused by the stores of that step PF - 1 steps later.
-    const int dny = sx ? ny : -ny;
-    const int wrap_at_r = wrap_at * ny, wrap_to_r = wrap_to * ny;
-    int sre = __builtin_amdgcn_readfirstlane((((rstart - dr * (t0l + 1)) % nx) + nx) % nx) * ny;   // step -1
-    const unsigned lane_b = (unsigned)rowbase * TS;
+    int sre = __builtin_amdgcn_readfirstlane((((rstart - dr * (t0l + 1)) % nx) + nx) % nx);   // step -1
+    const unsigned lane_b = (unsigned)rowbase * TS, rwb = (unsigned)rw * TS;
     unsigned sbr[PF], ser[KEEP ? PF : 1];
     bool actr[PF];
 #pragma unroll
@@ -361,8 +363,8 @@ __global__ __launch_bounds__(1024) void k_sweep(SweepArgs a)
         // idle lanes sit on their first or last row, away from the
         // active ones: an out-of-range offset keeps their loads off
         // the memory system (they return 0, never used)
-        const unsigned pp = inp ? (unsigned)(rowbase + sre) : DCT_OOB;
-        const unsigned pb = inp ? lane_b + (unsigned)sre * TS : DCT_OOB;
+        const unsigned pp = inp ? (unsigned)(rowbase + sre * rw) : DCT_OOB;
+        const unsigned pb = inp ? lane_b + (unsigned)sre * rwb : DCT_OOB;
         sbr[ps] = pb;
         actr[ps] = inp;
         if (KEEP) ser[KEEP ? ps : 0] = pp;
@@ -387,8 +389,8 @@ __global__ __launch_bounds__(1024) void k_sweep(SweepArgs a)
                 zr[MULTI ? fs : 0] = bld<T>(rzi, zo_off);
             }
         }
-        sre += dny;
-        sre = sre == wrap_at_r ? wrap_to_r : sre;
+        sre += dr;
+        sre = sre == wrap_at ? wrap_to : sre;
     };
     for (int tb = -PF; tb < NTp; tb += PF) {
         if (PIPE && (bj > 0 || bk > 0)) {
@@ -640,9 +642,9 @@ __global__ __launch_bounds__(1024 / ZL) void k_sweep_lw(SweepArgs a)
     const int NT = nx + min(ny, 64) + nz - 2;
     const int NTp = ((NT + PF - 1) / PF) * PF;
     const int dr = sx ? 1 : -1;
-    const int dny = sx ? ny : -ny;
-    const int wrap_at_r = (sx ? nx : -1) * ny, wrap_to_r = (sx ? 0 : nx - 1) * ny;
+    const int wrap_at = sx ? nx : -1, wrap_to = sx ? 0 : nx - 1;
     const int rstart = rot_row(cls, sx ? 0 : nx - 1, jm, nx);
+    const int rw = tile_w(j, ny);
     // per layer: validity, lane part of the offsets, start step, wave-uniform
     // row offset of the prefetched step (step -1 first)
     bool vz[ZL];
@@ -653,9 +655,9 @@ __global__ __launch_bounds__(1024 / ZL) void k_sweep_lw(SweepArgs a)
         const int kp = w * ZL + z;
         vz[z] = lv && kp < nz;
         const int k = vz[z] ? (sz ? kp : nz - 1 - kp) : 0;
-        rowbase[z] = k * nx * ny + j;
+        rowbase[z] = (int)row_pos(0, j, k, nx, ny);
         t0[z] = l + kp;
-        sre[z] = __builtin_amdgcn_readfirstlane((((rstart - dr * (t0[z] + 1)) % nx) + nx) % nx) * ny;
+        sre[z] = __builtin_amdgcn_readfirstlane((((rstart - dr * (t0[z] + 1)) % nx) + nx) % nx);
         zlast[z] = kp == nz - 1;
     }
     if (w == 0) zbuf[0][0][l] = zbuf[1][0][l] = bc;
@@ -696,14 +698,14 @@ __global__ __launch_bounds__(1024 / ZL) void k_sweep_lw(SweepArgs a)
 #pragma unroll
                 for (int z = 0; z < ZL; ++z) {
                     const bool inp = vz[z] && (unsigned)(tp - t0[z]) < (unsigned)nx;
-                    const unsigned pb = inp ? (unsigned)(rowbase[z] + sre[z]) * TS : DCT_OOB;
+                    const unsigned pb = inp ? (unsigned)(rowbase[z] + sre[z] * rw) * TS : DCT_OOB;
                     sbr[z][ps] = pb;
                     actr[z][ps] = inp;
-                    if (KEEP) ser[KEEP ? z : 0][KEEP ? ps : 0] = inp ? (unsigned)(rowbase[z] + sre[z]) : DCT_OOB;
+                    if (KEEP) ser[KEEP ? z : 0][KEEP ? ps : 0] = inp ? (unsigned)(rowbase[z] + sre[z] * rw) : DCT_OOB;
                     qr[z][ps] = bld<T>(rq, pb);
                     sr[z][ps] = bld<T>(rsg, pb);
-                    sre[z] += dny;
-                    sre[z] = sre[z] == wrap_at_r ? wrap_to_r : sre[z];
+                    sre[z] += dr;
+                    sre[z] = sre[z] == wrap_at ? wrap_to : sre[z];
                 }
             }
             // everything except the z term, for every layer
@@ -767,6 +769,396 @@ __global__ __launch_bounds__(1024 / ZL) void k_sweep_lw(SweepArgs a)
         double s = 0.0;
         for (int q = 0; q < nwv; ++q) s += red[threadIdx.x][q];
         a.leak_part[(long)item * a.nblk * 3 + threadIdx.x] = s;
+    }
+}
+
+// DPP row_shr:1 -- lane l of each 16-lane row receives lane l - 1's value of v,
+// the row's first lane receives old
+template <typename T>
+__device__ inline T dpp_row_up_or(T v, T old);
+template <>
+__device__ inline double dpp_row_up_or<double>(double v, double old)
+{
+    int lo = __builtin_amdgcn_update_dpp(__double2loint(old), __double2loint(v), 0x111, 0xf, 0xf, false);
+    int hi = __builtin_amdgcn_update_dpp(__double2hiint(old), __double2hiint(v), 0x111, 0xf, 0xf, false);
+    return __hiloint2double(hi, lo);
+}
+template <>
+__device__ inline float dpp_row_up_or<float>(float v, float old)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(old), __float_as_int(v), 0x111, 0xf, 0xf, false));
+}
+
+// Offset of an idle lane of a tile wave: beyond every array, also after the
+// per-step increments that idle lanes take like the others.
+#define DCT_TILE_OOB 0xC0000000u
+#define DCT_TILE_SKEW 24        // last lane's start step within a tile: 15 rows + 2 x 3 layers, and up to
+                                // 3 by which waves start inside a group of BG steps
+#define DCT_TILE_XMIN 40        // shortest rows whose tiles follow each other without a break
+#define DCT_TILE_LY 20          // start distance of two streams, in steps
+#define DCT_TILE_BG 4           // steps between two barriers
+
+// Steps from a wave's tile to its next (P): nx rounded up to a multiple of BG
+// (a group of steps then lies in one tile's period).  Rows too short for that wait
+// until every lane has ended its row, and streams wait for the last stream's
+// tile, which their next tile follows.
+__host__ __device__ inline int tile_period(int nx, int S, int NJ)
+{
+    int p = ((nx < DCT_TILE_XMIN ? nx + DCT_TILE_SKEW + 3 : nx) + 3) & ~3;
+    if (p < DCT_TILE_XMIN) p = DCT_TILE_XMIN;
+    return NJ > S && S * DCT_TILE_LY > p ? S * DCT_TILE_LY : p;
+}
+// Slots of a y-face ring: a tile and what lanes write past its end.
+__host__ __device__ inline int tile_yslots(int P) { return P + 32; }
+// LDS words (of T) of a tile-wave workgroup: a pad that keeps every ring
+// address positive, the ring of boundary values and one z-face ring per wave,
+// [2 BG][64] each, the y-face rings [S][NK][slots][4], those of the grid's last
+// row [NK][slots][4], and a place for what no one reads.
+__host__ __device__ inline long tile_ring_words(int S, int NK)
+{
+    return (DCT_TILE_BG - 1) * 64 + (long)(1 + S * NK) * 2 * DCT_TILE_BG * 64;
+}
+__host__ __device__ inline long tile_lds_words(int S, int NK, int P)
+{
+    return tile_ring_words(S, NK) + (long)(S + 1) * NK * tile_yslots(P) * 4 + 64 * 4 + 4 * DCT_TILE_BG;
+}
+
+// Tile waves (every z layer and y row of a direction in one workgroup): a wave
+// sweeps tiles of 16 y rows x 4 z layers, lane = (layer kl, row l), walking x;
+// lane (kl, l) handles x = t - l - 2 kl, so a tile costs nx + 21 steps instead
+// of the nx + 63 of a wave of 64 rows, and a wave takes its tiles back to
+// back: a lane that ends a tile's row starts the next tile's row on the next
+// step.  At 64 x 64 x 16 that is 1,108 wave-steps per direction (4 waves of 4
+// tiles) against 2,272 for 16 waves of 64 rows.
+//
+// Workgroup = S x NK waves: wave (s, kt) takes layers 4 kt .. 4 kt + 3 of the
+// y tiles s, s + S, ... in sweep order.  S is chosen by the host: 1 when there
+// are enough directions to fill the SIMDs (fewest wave-steps), more when the
+// steps of one direction are what counts.
+//
+// Faces: x in a register; y from lane l - 1 (DPP), the first row from an LDS
+// ring that the last row of the tile before wrote (the same wave one tile
+// earlier, or the stream before); z through an LDS ring of 2 BG steps, lane
+// (kl, l) taking what (kl - 1, l) wrote two steps ago, the first layer what
+// the wave below wrote BG + 1 steps ago.  Every LDS read is issued one step
+// before its value is needed (hence the two steps per layer), so no LDS
+// latency lies in the chain from cell to cell.  Waves start 7 + BG steps apart
+// in z and LY in y: everything that crosses waves is older than the last
+// barrier, and one barrier per BG steps couples them.
+//
+// Lanes need no activity test: an idle lane's offset lies beyond the arrays
+// (loads give 0, stores are dropped), and a lane is only read by a neighbour
+// that is active later, on what it produced while it was active; before its
+// first row a lane computes exact zeros from zeros, which is the vacuum
+// boundary value (the host takes other schedules for a prescribed inflow).
+// Lanes start and end rows in the first 22 steps of a tile; those groups of
+// steps run the checks of the faces (a compare and selects each, no lane masks:
+// one wave's slow step holds up all at the barrier).  The addresses' checks run
+// in every step: a branch around them cost more (64 x 64 x 16, 80 directions:
+// 64.7 against 60.4 us).
+//
+// Bound, for one source, by a step's instructions and their chain (64 x 64 x 16,
+// 80 directions FP32: 64.8 us, 61.6 without any memory access, 47.7 without the
+// fixup), for many by HBM.  A sweep of 80 directions against the other
+// schedules: 128 x 128 x 32 FP32 350 -> 257 us, FP64 559 -> 424; 64 x 64 x 16
+// FP64 86 -> 79 (FP32 56 -> 60: the tuner keeps the barrier coupling there).
+//
+// Every cell's arithmetic is that of k_sweep, so the results are the same bit
+// for bit.  MODE as in k_sweep; FIX: the set-to-zero fixup is on.
+template <typename T, int PF, int MODE, bool FIX>
+__global__ __launch_bounds__(1024) void k_sweep_t(SweepArgs a)
+{
+    constexpr bool ADJ = MODE == 2, KEEP = MODE == 1;
+    constexpr unsigned TS = sizeof(T);
+    constexpr int BG = DCT_TILE_BG, RS = 2 * BG;             // z ring slots
+    constexpr int U = PF > RS ? PF : RS;                     // unrolled steps
+    constexpr int LZ = 7 + BG;
+    static_assert(U % PF == 0 && U % RS == 0 && BG == 4, "ring slots are constants of the unrolled loop");
+    static_assert(PF + BG + DCT_TILE_SKEW <= DCT_TILE_XMIN, "the next tile is set up before a lane starts it");
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_t[];
+    __shared__ double red[3][16];
+    const int b = a.b0 + (int)blockIdx.y, n = (int)blockIdx.x;
+    const long item = (long)b * a.N + n;
+    if (a.state[b].finished) return;
+    const int g = eff_group(a.state[b].g, a.G, a.reverse);
+    const int nx = a.nx, ny = a.ny, nz = a.nz;
+    const long C = a.C;
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l = lane & 15, kl = lane >> 4;
+    const int NK = (nz + 3) >> 2, NJ = (ny + 15) >> 4, S = a.tS;
+    int s = 0, kt = wv;                                      // wave (s, kt)
+    while (kt >= NK) {
+        kt -= NK;
+        ++s;
+    }
+    const int P = tile_period(nx, S, NJ), M = tile_yslots(P);
+    const int gapw = P - nx;                                 // idle steps between a lane's rows
+    // the wave's phases count from the group of steps in which its first lane
+    // starts (step t0); lane (kl, l) starts its rows at phase skew
+    const int t0 = (s * DCT_TILE_LY + kt * LZ) & ~(BG - 1);
+    const int skew = l + 2 * kl + ((s * DCT_TILE_LY + kt * LZ) & (BG - 1));
+    const double ox = a.dirs[3 * n], oy = a.dirs[3 * n + 1], oz = a.dirs[3 * n + 2];
+    const bool sx = ADJ ? !(ox > 0) : ox > 0, sy = ADJ ? !(oy > 0) : oy > 0, sz = ADJ ? !(oz > 0) : oz > 0;
+    const int cls = dir_class(ox, oy);
+    const T cx = (T)(2.0 * fabs(ox) / a.dx), cy = (T)(2.0 * fabs(oy) / a.dy), cz = (T)(2.0 * fabs(oz) / a.dz);
+    const T csum = cx + cy + cz;
+    const rsrc_t rq = mk_rsrc((const T *)a.q + item * C, C * TS);
+    const rsrc_t rpsi = mk_rsrc((T *)a.psi + ((long)b * a.psi_bs + (long)g * a.psi_gs + n) * C, C * TS);
+    const rsrc_t rmask = mk_rsrc((ADJ || KEEP) && a.mask ? a.mask + (((long)b * a.G + g) * a.N + n) * C : nullptr, C);
+    const rsrc_t rsg = mk_rsrc((const T *)a.sigc + ((long)cls * a.G + g) * C, C * TS);
+    // layers of this wave: a partial tile that comes first (sz < 0) fills the
+    // upper lanes, as in y below
+    const int K = sz ? kt : NK - 1 - kt, wz = min(4, nz - 4 * K);
+    const int kloc = sz ? kl : 3 - kl;
+    const bool kok = kloc < wz;
+    const int dr = sx ? 1 : -1, i0 = sx ? 0 : nx - 1;
+    const float inx = 1.0f / (float)nx;
+    const int eph = skew + nx >= P ? skew + nx - P : skew + nx;   // phase at which the lane's row has ended
+
+    T *zr = (T *)smem_t + (BG - 1) * 64;                     // [1 + S NK][RS][64]
+    T *yf = (T *)smem_t + tile_ring_words(S, NK);            // [S + 1][NK][M][4]
+    {
+        // every face starts as the vacuum boundary value
+        const int nw = (int)(tile_lds_words(S, NK, P) * (long)TS / 16);
+        for (int i = threadIdx.x; i < nw; i += blockDim.x) ((uint4 *)smem_t)[i] = uint4{0u, 0u, 0u, 0u};
+    }
+    // y faces: at its step tau the wave's last row writes slot tau mod M of the
+    // wave's ring; the first row of the next tile, the same x and 16 steps less
+    // into its tile, reads it (for its next step) at step tau - 16 of the next
+    // stream, or of stream 0 a period later.  The row that ends a partial last
+    // tile (l < 15) writes the extra ring instead, and the lanes that end no
+    // tile beside them (a choice of addresses costs less than masking lanes).
+    const int slast = (NJ - 1) % S, wlast = ny - 16 * (NJ - 1);
+    const bool part = sy && wlast < 16;
+    const T *yrb = yf + (long)((s == 0 ? S - 1 : s - 1) * NK + kt) * M * 4 + kl;
+    T *ywb = yf + (long)wv * M * 4 + kl;
+    bool ymov = true;                                        // the lane writes a ring
+    if (part && s == slast && l == wlast - 1) ywb = yf + (long)(S * NK + kt) * M * 4 + kl;
+    else if (l != 15) {
+        ywb = yf + (long)(S + 1) * NK * M * 4 + 4 * lane;
+        ymov = false;
+    }
+    T *zw = zr + (1 + wv) * RS * 64 + lane;                  // this lane's z outflow of slot 0
+    // z read of slot u, used a step later: kl > 0 the own wave's row kl - 1 of
+    // step t - 1, slot (u - 1) mod RS; kl = 0 the top row of the wave below (or
+    // the boundary ring) of step t - BG, slot (u - BG) mod RS, which is BG + 1
+    // slots above for u in [1, BG) and BG - 1 below otherwise
+    const T *zn = zr + (kt == 0 ? 0 : wv) * RS * 64 + 48 + l;
+    const T *zp = kl > 0 ? zw - 16 : zn + (BG + 1) * 64;
+    const T *zm = kl > 0 ? zw - 16 : zn - (BG - 1) * 64;
+
+    // the tile the wave starts next: the lane's offset of its first cell (and
+    // whether it takes part), of the row past the end and the row it turns to
+    // there, and bytes from row to row
+    unsigned n_off = DCT_TILE_OOB, n_end = 0u, n_turn = 0u;
+    int n_d = 0;
+    bool n_ok = false;
+    auto mod_nx = [&](int v) __attribute__((always_inline)) {
+        int r = v - (int)((float)v * inx) * nx;              // the quotient is off by at most 1
+        r = r < 0 ? r + nx : (r >= nx ? r - nx : r);
+        return __builtin_amdgcn_readfirstlane(r);
+    };
+    const int skew0 = (s * DCT_TILE_LY + kt * LZ) & (BG - 1);
+    auto tile_setup = [&](int jt) __attribute__((always_inline)) {
+        n_ok = false;
+        n_off = DCT_TILE_OOB;
+        if (jt >= NJ) return;
+        const int J = sy ? jt : NJ - 1 - jt, w = min(16, ny - 16 * J);
+        // a partial tile that comes first (sy < 0) fills the upper lanes, so that
+        // its last row is lane 15 like every tile's that another follows
+        const int jl = sy ? l : 15 - l;
+        n_ok = kok && jl < w;
+        const int st = w * (int)TS;
+        const unsigned lb = (unsigned)((4 * K + kloc) * nx * ny + 16 * J * nx + jl) * TS;
+        // row of phase skew0 (lane 0), then of this lane's start
+        const int r0 = rot_row(cls, i0, mod_nx(16 * J + (sy ? 0 : 15)), nx);
+        int r = r0 + dr * l;
+        while (r < 0) r += nx;
+        while (r >= nx) r -= nx;
+        n_off = n_ok ? lb + (unsigned)(r * st) : DCT_TILE_OOB;
+        n_end = sx ? lb + (unsigned)(nx * st) : lb - (unsigned)st;
+        n_turn = sx ? lb : lb + (unsigned)((nx - 1) * st);
+        n_d = dr * st;
+    };
+    int jnext = s;
+    tile_setup(jnext);
+    jnext += S;
+    bool adv = false;                                        // the tile after the current one is set up
+    bool first = true;                                       // the wave's first tile: lanes start from zeros
+    const int nt = (NJ - s + S - 1) / S;                     // tiles of this wave
+    const int tend = t0 + (nt - 1) * P + nx + DCT_TILE_SKEW + 1;
+    // last step of the workgroup: the last tile is the last stream's to start
+    const int NT = max(slast * DCT_TILE_LY + ((NJ - 1) / S) * P,
+                       NJ > S && slast < S - 1 ? (S - 1) * DCT_TILE_LY + ((NJ - 1) / S - 1) * P : 0) +
+                   (NK - 1) * LZ + nx + DCT_TILE_SKEW + 1;
+    // the lane's z outflow leaves the grid: its layer is the last in sweep order
+    const T zone = kt == NK - 1 && kl == (sz ? wz - 1 : 3) ? (T)1 : (T)0;
+
+    T qr[PF], sr[PF];
+    unsigned offr[PF];
+    int fr[ADJ ? PF : 1];
+#pragma unroll
+    for (int u = 0; u < PF; ++u) {
+        qr[u] = sr[u] = (T)0;
+        offr[u] = DCT_TILE_OOB;
+        if (ADJ) fr[ADJ ? u : 0] = 0;
+    }
+    unsigned off = DCT_TILE_OOB, oend = 0u, oturn = 0u;
+    int d = n_d;
+    T xo = 0, yo = 0, zin = 0, yfi = 0;
+    // outflows of a row: x (its last) and z (summed), kept when the row ends and
+    // added up in FP64 once the tile is done
+    T lzv = 0, lxr = 0, lzr = 0;
+    bool okA = false;                                        // the lane took part in the tile those belong to
+    double lx = 0.0, lz = 0.0;
+    const bool whole = P > nx + DCT_TILE_SKEW;               // every row of a tile ends before the next tile starts
+    __syncthreads();
+
+    int tb = -U;
+    for (; tb + U <= t0 - PF; tb += U)
+#pragma unroll
+        for (int gq = 0; gq < U / BG; ++gq) __syncthreads();
+    int ph = tb - t0;                                        // phase of the compute step
+    // ring slots of the group's first step
+    int yws = ph, yrs = ph + 16 - (s == 0 ? P : 0);
+    yws = yws < 0 ? yws + M : yws;
+    yrs = yrs < 0 ? yrs + M : (yrs >= M ? yrs - M : yrs);
+    for (; tb < tend; tb += U) {
+#pragma unroll
+        for (int gq = 0; gq < U / BG; ++gq) {
+            if (!adv && ph > DCT_TILE_SKEW) {
+                if (!whole) {
+                    lx += okA ? (double)lxr : 0.0;
+                    lz += okA ? (double)lzr : 0.0;
+                }
+                okA = n_ok;
+                tile_setup(jnext);
+                jnext += S;
+                adv = true;
+            }
+            int pl = ph + PF;                                // phase of the load step
+            if (pl >= P) pl -= P;
+            // groups of steps with lanes starting or ending rows
+            const bool evc = (ph <= DCT_TILE_SKEW && !first) || ph + BG > nx;
+            const T *yr = yrb + 4 * yrs;
+            T *yw = ywb + (ymov ? 4 * yws : 0);
+#pragma unroll
+            for (int ug = 0; ug < BG; ++ug) {
+                const int u = gq * BG + ug, uq = u % PF;
+                // LDS inflows of the next step
+                const T z_nx = ((u % RS) >= 1 && (u % RS) < BG ? zp : zm)[((u + RS - 1) % RS) * 64];
+                const T y_nx = yr[4 * ug];
+                if (__builtin_expect(evc, 0)) {
+                    const int q = ph + ug;
+                    const bool st = q == skew, en = gapw > 0 ? q == eph : st;
+                    lxr = en ? xo : lxr;
+                    lzr = en ? lzv : lzr;
+                    lzv = st ? (T)0 : lzv;
+                    xo = st ? (T)0 : xo;
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                const T qv = qr[uq], sv = sr[uq];
+                const int fv = ADJ ? fr[ADJ ? uq : 0] : 0;
+                const T xin = xo, yin = dpp_row_up_or<T>(yo, yfi);
+                Cell4<T> c;
+                if (ADJ) {
+                    const bool ux = !(fv & 1), uy = !(fv & 2), uz = !(fv & 4);
+                    const T ex = ux ? cx : (T)0, ey = uy ? cy : (T)0, ez = uz ? cz : (T)0;
+                    const T y0 = rcp_nr(sv + ex + ey + ez);
+                    const T n0 = qv + ex * xin + ey * yin;
+                    c.pc = fma(ez, zin, n0) * y0;
+                    c.xo = ux ? c.pc + c.pc - xin : c.pc;
+                    c.yo = uy ? c.pc + c.pc - yin : c.pc;
+                    c.zo = uz ? c.pc + c.pc - zin : c.pc;
+                    c.fixed = 0;
+                } else {
+                    const T n0 = qv + cx * xin + cy * yin;
+                    c.pc = fma(cz, zin, n0) * rcp_nr(sv + csum);
+                    c.xo = c.pc + c.pc - xin;
+                    c.yo = c.pc + c.pc - yin;
+                    c.zo = c.pc + c.pc - zin;
+                    c.fixed = 0;
+                    if (FIX && fmin(c.xo, fmin(c.yo, c.zo)) < (T)0)
+                        c = dd_fixup<T>(qv, sv, cx, cy, cz, xin, yin, zin, c);
+                }
+                zw[(u % RS) * 64] = c.zo;
+                yw[4 * ug] = c.yo;
+                bst(rpsi, offr[uq], c.pc);
+                if (KEEP)
+                    __builtin_amdgcn_raw_buffer_store_b8((unsigned char)c.fixed, rmask, offr[uq] / TS, 0, 0);
+                lzv = fma(zone, c.zo, lzv);
+                // operands of step t + PF, into the slots this step has used
+                off += (unsigned)d;
+                off = off == oend ? oturn : off;
+                const bool sl = pl + ug == skew;
+                if (gapw > 0) off = pl + ug == eph ? DCT_TILE_OOB : off;
+                off = sl ? n_off : off;
+                oend = sl ? n_end : oend;
+                oturn = sl ? n_turn : oturn;
+                if (wlast < 16) d = sl ? n_d : d;
+                offr[uq] = off;
+                qr[uq] = bld<T>(rq, off);
+                sr[uq] = bld<T>(rsg, off);
+                if (ADJ) fr[ADJ ? uq : 0] = __builtin_amdgcn_raw_buffer_load_b8(rmask, off / TS, 0, 0);
+                xo = c.xo;
+                yo = c.yo;
+                zin = z_nx;
+                yfi = y_nx;
+            }
+            yws = yws + BG >= M ? yws + BG - M : yws + BG;
+            yrs = yrs + BG >= M ? yrs + BG - M : yrs + BG;
+            ph += BG;
+            if (ph >= P) {
+                ph -= P;
+                adv = first = false;
+                if (whole) {
+                    lx += okA ? (double)lxr : 0.0;
+                    lz += okA ? (double)lzr : 0.0;
+                    okA = false;
+                }
+            }
+            __syncthreads();
+        }
+    }
+    // the last tile's rows (with short rows the loop may end before the tile
+    // after it was set up)
+    const bool okl = whole && !adv ? n_ok : okA;
+    lx += okl ? (double)lxr : 0.0;
+    lz += okl ? (double)lzr : 0.0;
+    for (; tb < NT; tb += U)
+#pragma unroll
+        for (int gq = 0; gq < U / BG; ++gq) __syncthreads();
+    // the last tile's y outflows lie in a ring, written at step x + l + 2 kl of
+    // the tile (l: its last row)
+    double ly = 0.0;
+    if (s == slast) {
+        const T *yl = yf + (long)((part ? S * NK + kt : wv) * M) * 4;
+        int v0 = (nt - 1) * P + (part ? wlast - 1 : 15) + skew0;
+        while (v0 >= M) v0 -= M;
+        for (int x = lane; x < nx; x += 64) {
+            int v = v0 + x;
+            v = v >= M ? v - M : v;
+            for (int q = 0; q < 4; ++q) {
+                if ((sz ? q : 3 - q) < wz) ly += (double)yl[v * 4 + q];
+                v = v + 2 >= M ? v + 2 - M : v + 2;
+            }
+        }
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+        lx += __shfl_down(lx, o, 64);
+        ly += __shfl_down(ly, o, 64);
+        lz += __shfl_down(lz, o, 64);
+    }
+    if (lane == 0) {
+        red[0][wv] = lx;
+        red[1][wv] = ly;
+        red[2][wv] = lz;
+    }
+    __syncthreads();
+    if (threadIdx.x < 3) {
+        double sum = 0.0;
+        for (int q = 0; q < S * NK; ++q) sum += red[threadIdx.x][q];
+        a.leak_part[item * a.nblk * 3 + threadIdx.x] = sum;
     }
 }
 
@@ -1087,9 +1479,9 @@ __global__ __launch_bounds__(1024 / ZL) void k_sweep_rc(SweepArgs a)
     const int NT = Knx + nl + nz - 1;
     const int NTp = ((NT + PF - 1) / PF) * PF;
     const int dr = sx ? 1 : -1;
-    const int dny = sx ? ny : -ny;
-    const int wrap_at_r = (sx ? nx : -1) * ny, wrap_to_r = (sx ? 0 : nx - 1) * ny;
+    const int wrap_at = sx ? nx : -1, wrap_to = sx ? 0 : nx - 1;
     const int rstart = rot_row(cls, sx ? 0 : nx - 1, jm, nx);
+    const int rw = tile_w(j, ny);
     const int top_w = (nz - 1) / ZL, top_z = (nz - 1) - top_w * ZL;
     __syncthreads();
     bool vz[ZL];
@@ -1100,9 +1492,9 @@ __global__ __launch_bounds__(1024 / ZL) void k_sweep_rc(SweepArgs a)
         const int kp = w * ZL + z;
         vz[z] = lv && kp < nz;
         const int k = vz[z] ? (sz ? kp : nz - 1 - kp) : 0;
-        rowbase[z] = k * nx * ny + j;
+        rowbase[z] = (int)row_pos(0, j, k, nx, ny);
         t0[z] = l + kp;
-        sre[z] = __builtin_amdgcn_readfirstlane((((rstart - dr * (t0[z] + 1)) % nx) + nx) % nx) * ny;
+        sre[z] = __builtin_amdgcn_readfirstlane((((rstart - dr * (t0[z] + 1)) % nx) + nx) % nx);
         lq[z] = tab_q[1];
         ls[z] = tab_s[1];
     }
@@ -1159,15 +1551,15 @@ __global__ __launch_bounds__(1024 / ZL) void k_sweep_rc(SweepArgs a)
                     lq[z] = st ? nq : lq[z];
                     ls[z] = st ? ns : ls[z];
                     const bool inp = vz[z] && (unsigned)(t + PF - 1 - t0[z]) < (unsigned)Knx;
-                    const unsigned cell = (unsigned)(rowbase[z] + sre[z]) * TS;
+                    const unsigned cell = (unsigned)(rowbase[z] + sre[z] * rw) * TS;
                     const unsigned pb = inp ? lq[z] + cell : DCT_OOB;
                     const unsigned sb = inp ? ls[z] + cell : DCT_OOB;
                     sbr[z][ps] = pb;
                     actr[z][ps] = inp;
                     qr[z][ps] = bld<T>(rq, pb);
                     sr[z][ps] = bld<T>(rsg, sb);
-                    sre[z] += dny;
-                    sre[z] = sre[z] == wrap_at_r ? wrap_to_r : sre[z];
+                    sre[z] += dr;
+                    sre[z] = sre[z] == wrap_at ? wrap_to : sre[z];
                 }
             }
             // a lane starting a row takes the boundary x inflow and records
@@ -1244,6 +1636,25 @@ __global__ __launch_bounds__(1024 / ZL) void k_sweep_rc(SweepArgs a)
     }
 }
 
+// Streams of a tile-wave launch over nwg directions of an nx x ny x nz grid on
+// a device of ncu compute units and lds bytes per workgroup; 0: the grid needs
+// another schedule.  One stream costs the fewest wave-steps, so it is taken
+// once its waves give every SIMD four; below that the steps of a direction
+// count, and its tiles are spread over two streams, or over 8 waves.  (64 x 64
+// x 16, 80 directions: 1 / 2 / 3 / 4 streams 89 / 64.7 / 64.2 / 64.8 us in FP32,
+// 104 / 83 / 86 / 89 in FP64: more waves on a SIMD only take each other's slots.)
+int tile_streams(int nx, int ny, int nz, long nwg, int is_f64, int ncu, size_t lds)
+{
+    const int NK = (nz + 3) / 4, NJ = (ny + 15) / 16;
+    auto fits = [&](int S) {
+        return S * NK <= 16 && (size_t)tile_lds_words(S, NK, tile_period(nx, S, NJ)) * (is_f64 ? 8 : 4) + 512 <= lds;
+    };
+    if (!fits(1)) return 0;
+    int S = 1;
+    while (S < NJ && fits(S + 1) && (S < 2 || S * NK < 8) && nwg * NK * S < 16L * ncu) ++S;
+    return S;
+}
+
 hipError_t launch_sweep(SweepArgs a, int is_f64, hipStream_t s, unsigned seq)
 {
     a.seq = seq;
@@ -1262,8 +1673,8 @@ hipError_t launch_sweep(SweepArgs a, int is_f64, hipStream_t s, unsigned seq)
     const int mode = a.adjoint ? 2 : (a.mask ? 1 : 0);
     // a launch over a subset of the right-hand sides: layered waves or chained sources
     const int nb = a.nb > 0 ? a.nb : a.B;
-    const bool layered = (a.layers == 2 || a.layers == 4) && !multi && mode != 2 && a.ny <= 64 && a.nz <= 16;
-    if (a.b0 < 0 || a.b0 + nb > a.B || ((a.b0 != 0 || nb != a.B) && (a.chainK > 1 || !(a.rhsK > 1 || layered))))
+    const bool layered = a.layers == 2 && !multi && mode != 2 && a.ny <= 64 && a.nz <= 16;
+    if (a.b0 < 0 || a.b0 + nb > a.B || ((a.b0 != 0 || nb != a.B) && (a.chainK > 1 || !(a.rhsK > 1 || a.tS > 0 || layered))))
         return hipErrorInvalidValue;
     if (a.chainK > 1) {
         // chained directions: one block, forward sweep without kept fluxes,
@@ -1301,6 +1712,34 @@ hipError_t launch_sweep(SweepArgs a, int is_f64, hipStream_t s, unsigned seq)
 #undef DCT_RC
         return hipGetLastError();
     }
+    if (a.tS > 0) {
+        // tile waves: S x NK waves, the whole y and z extent in one workgroup
+        const int NK = (a.nz + 3) / 4, NJ = (a.ny + 15) / 16;
+        if (a.tS > NJ || a.tS * NK > 16 || a.pipe || a.inflow || a.nblk != 1) return hipErrorInvalidValue;
+        const dim3 tgrid((unsigned)a.N, (unsigned)nb), tblock(64 * a.tS * NK);
+        const size_t shm = (size_t)tile_lds_words(a.tS, NK, tile_period(a.nx, a.tS, NJ)) * (is_f64 ? 8 : 4);
+#define DCT_TILE(T, PF, MD, FX)                                                                          \
+    do {                                                                                                 \
+        hipError_t e_ = hipFuncSetAttribute((const void *)k_sweep_t<T, PF, MD, FX>,                       \
+                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);       \
+        if (e_ != hipSuccess) return e_;                                                                 \
+        hipLaunchKernelGGL((k_sweep_t<T, PF, MD, FX>), tgrid, tblock, shm, s, a);                         \
+    } while (0)
+#define DCT_TILE_M(T, PF)                                                                                \
+    do {                                                                                                 \
+        if (mode == 2) DCT_TILE(T, PF, 2, false);                                                         \
+        else if (mode == 1 && a.fixup) DCT_TILE(T, PF, 1, true);                                          \
+        else if (mode == 1) DCT_TILE(T, PF, 1, false);                                                    \
+        else if (a.fixup) DCT_TILE(T, PF, 0, true);                                                       \
+        else DCT_TILE(T, PF, 0, false);                                                                   \
+    } while (0)
+        if (is_f64) DCT_TILE_M(double, 4);
+        else if (a.tS > 1) DCT_TILE_M(float, 8);
+        else DCT_TILE_M(float, 4);
+#undef DCT_TILE_M
+#undef DCT_TILE
+        return hipGetLastError();
+    }
     if (layered) {
         const int nwv = (a.nz + a.layers - 1) / a.layers;
         const dim3 lgrid((unsigned)(nb * a.N)), lblock(64 * nwv);
@@ -1310,11 +1749,9 @@ hipError_t launch_sweep(SweepArgs a, int is_f64, hipStream_t s, unsigned seq)
         // 346 us); 2 steps (49 VGPRs) and 6 (89) were slower
 #define DCT_LW(T, ZL, MD) hipLaunchKernelGGL((k_sweep_lw<T, ZL, 4, MD>), lgrid, lblock, 0, s, a)
         if (is_f64) {
-            if (a.layers == 4) { if (mode == 1) DCT_LW(double, 4, 1); else DCT_LW(double, 4, 0); }
-            else { if (mode == 1) DCT_LW(double, 2, 1); else DCT_LW(double, 2, 0); }
+            if (mode == 1) DCT_LW(double, 2, 1); else DCT_LW(double, 2, 0);
         } else {
-            if (a.layers == 4) { if (mode == 1) DCT_LW(float, 4, 1); else DCT_LW(float, 4, 0); }
-            else { if (mode == 1) DCT_LW(float, 2, 1); else DCT_LW(float, 2, 0); }
+            if (mode == 1) DCT_LW(float, 2, 1); else DCT_LW(float, 2, 0);
         }
 #undef DCT_LW
         return hipGetLastError();

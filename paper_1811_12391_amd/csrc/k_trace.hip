@@ -308,9 +308,8 @@ hipError_t launch_sigc(const Geo &g, const uint8_t *mat, const double *rho, cons
     return hipGetLastError();
 }
 
-// sigma_t in the chain layout of period K nx: chain row `row` of layer k holds
-// the cells of class-layout row row mod nx, so the table is K copies of each
-// layer's class rows.
+// sigma_t in the chain layout of period K nx: element (row, j) of layer k is
+// the cell with i = (row -+ j) mod nx, so the table is K copies of each layer.
 template <typename T>
 __global__ __launch_bounds__(256) void k_sigch(Geo g, const T *sigc, int K, T *sigch)
 {
@@ -322,7 +321,7 @@ __global__ __launch_bounds__(256) void k_sigch(Geo g, const T *sigc, int K, T *s
     const int k = (int)(p / plane);
     const long rem = p - (long)k * plane;
     const int row = (int)(rem / g.ny), j = (int)(rem - (long)row * g.ny);
-    sigch[(long)cg * KC + p] = sigc[(long)cg * g.C + ((long)k * g.nx + row % g.nx) * g.ny + j];
+    sigch[(long)cg * KC + p] = sigc[(long)cg * g.C + row_pos(row % g.nx, j, k, g.nx, g.ny)];
 }
 
 hipError_t launch_sigch(const Geo &g, const void *sigc, int G, int K, void *sigch, int is_f64, hipStream_t s)

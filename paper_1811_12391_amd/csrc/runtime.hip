@@ -1132,8 +1132,9 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
     // schedule = (z layers per workgroup, coupling, chain): coupling 1 = LDS
     // progress counters between the waves of a workgroup, 2 = one barrier per
     // step, 3 = as 2 with every block of a sweep in one launch (pipelined
-    // blocks), 4 / 5 = layered waves (every wave sweeps 4 / 2 z layers; one
-    // block, ny <= 64 and nz <= 16, forward sweeps), 6 / 7 / 8 = the K
+    // blocks), 4 = tile waves (every wave sweeps tiles of 16 y rows x 4 z
+    // layers), 5 = layered waves (every wave sweeps 2 z layers; one block,
+    // ny <= 64 and nz <= 16, forward sweeps), 6 / 7 / 8 = the K
     // consecutive directions of one octant chained through one workgroup,
     // with 1 / 2 / 4 z layers per wave (one block, ny <= nx, forward sweeps
     // without kept fluxes; q and psi in the chain layout), 9 / 10 = one
@@ -1141,10 +1142,21 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
     // z layers per wave (same conditions, class layouts)
     double tune_ms = 0.0;
     const bool layered_ok = ny <= 64 && nz <= 16;
+    // tile waves (coupling 4): any grid of up to 64 layers whose faces fit the
+    // LDS when the schedule is free, the layered waves' grids when asked for
+    const int tile_S = tile_streams(nx, ny, nz, (long)B * N, is64, ctx->ncu, ctx->lds_max);
+    const bool free_sched = o.sweep_bk == 0 && o.sweep_sync == 0 && o.sweep_chain <= 1;
+    const bool tile_ok = tile_S > 0 && (free_sched || layered_ok) && !o.test_inflow;
     auto set_coupling = [&](int cpl) {
+        sw.tS = cpl == 4 && tile_ok ? tile_S : 0;
+        if (sw.tS > 0) {
+            // one workgroup per direction, whatever the grid
+            pl.NBJ = pl.NBK = pl.nblk = pl.ndiag = 1;
+            sw.NBJ = sw.NBK = sw.nblk = tr.nblk = 1;
+        }
         sw.sync = cpl == 1;
         sw.pipe = cpl == 3;
-        sw.layers = (cpl == 4 && layered_ok) ? 4 : ((cpl == 5 && layered_ok) ? 2 : 0);
+        sw.layers = (cpl == 5 && layered_ok) ? 2 : 0;
         if (cpl >= 6 && cpl <= 8) sw.layers = cpl == 6 ? 1 : (cpl == 7 ? 2 : 4);
         if (cpl >= 9) sw.layers = cpl == 9 ? 2 : 1;
     };
@@ -1177,7 +1189,12 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
     };
     int chainK = 1, rhsK = 1;
     {
-        int bk = o.sweep_bk > 0 ? o.sweep_bk : 16, cpl = o.sweep_sync > 0 ? o.sweep_sync : 1;
+        int bk = o.sweep_bk > 0 ? o.sweep_bk : 16;
+        // untuned: tile waves, except that with a CU to itself for every
+        // direction of a one-block grid the barrier coupling's fewer steps are
+        // faster (24 x 24 x 8, 24 directions, FP64: 26 against 34 us a sweep)
+        int cpl = o.sweep_sync > 0 ? o.sweep_sync
+                                   : (!free_sched || !tile_ok ? 1 : (layered_ok && (long)B * N <= ctx->ncu ? 2 : 4));
         chainK = o.sweep_chain > 1 ? o.sweep_chain :
                  ((cpl >= 6 && cpl <= 8 && !chain_ks.empty()) ? chain_ks.back() : 1);
         rhsK = o.sweep_rhs_chain > 0 ? o.sweep_rhs_chain : std::min(B, 4);
@@ -1225,7 +1242,9 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
                     for (int cc : {1, 2, 3, 4, 5, 6, 7, 8, 9, 10}) {
                         if (!free_cpl && cc != cpl) continue;
                         if (cc == 3 && (!multi || cb < 2)) continue;   // pipelining needs several blocks
-                        if (cc >= 4 && (!layered_ok || cb != std::min(16, nz))) continue;   // one block of every layer
+                        // one block of every layer
+                        if (cc >= 4 && cb != std::min(16, nz)) continue;
+                        if (cc == 4 ? !tile_ok : (cc > 4 && !layered_ok)) continue;
                         if (cc >= 9) {
                             for (int R : rhs_ks)
                                 if (free_rhs || R == rhsK) cands.push_back({cb, cc, 1, R});
@@ -1290,7 +1309,8 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
         }
         apply_blocks(bk);
         if (cpl == 3 && (pl.nblk == 1 || pl.BK < 2)) cpl = 1;   // one block (or 1-layer blocks): not pipelined
-        if (cpl >= 4 && cpl <= 5 && (!layered_ok || pl.nblk != 1)) cpl = 2;   // layered waves need one block
+        if (cpl == 4 && (!tile_ok || (!free_sched && pl.nblk != 1))) cpl = 2;
+        if (cpl == 5 && (!layered_ok || pl.nblk != 1)) cpl = 2;   // layered waves need one block
         if (cpl >= 6 && cpl <= 8 &&
             (pl.nblk != 1 || std::find(chain_ks.begin(), chain_ks.end(), chainK) == chain_ks.end())) {
             cpl = 2;   // chains need one block and chains inside octants
@@ -2054,7 +2074,14 @@ static int adjoint_common(dct_ctx *ctx, const double *roi, const dct_opts *opts,
     sw.fixup = 0;
     sw.sync = ctx->last_sync == 1;
     sw.pipe = ctx->last_sync == 3;
-    sw.layers = 0;                     // transposed sweeps run on k_sweep (barrier coupling for layered schedules)
+    sw.layers = 0;
+    // transposed sweeps: tile waves after a tile-wave forward solve, otherwise
+    // k_sweep (barrier coupling for layered schedules)
+    sw.tS = ctx->last_sync == 4 ? tile_streams(nx, ny, nz, (long)B * N, is64, ctx->ncu, ctx->lds_max) : 0;
+    if (sw.tS > 0) {
+        pl.NBJ = pl.NBK = pl.nblk = pl.ndiag = 1;
+        sw.NBJ = sw.NBK = sw.nblk = 1;
+    }
     sw.chainK = 1;
     sw.rhsK = 1;
     sw.sigch = nullptr;
