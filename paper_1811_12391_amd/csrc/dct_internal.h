@@ -33,6 +33,7 @@
 #define DCT_MAXMAT 8
 #define DCT_MAXL 5
 #define DCT_MAXNM ((DCT_MAXL + 1) * (DCT_MAXL + 1))
+#define DCT_CNT_LINES 128       // completion counters (of 32 workgroups or blocks each) per right-hand side
 #define DCT_MAXCHAIN 16   // directions chained through one sweep workgroup
 #define DCT_MAXRC 8       // right-hand sides chained through one sweep workgroup
 #define DCT_PI 3.14159265358979323846
@@ -349,7 +350,9 @@ struct CombArgs {
     int stall_window;         // reduced-precision stagnation stop (0 = off)
     int nblocks_per_b;
     int reverse;              // groups run from G-1 down to 0
-    unsigned *cnt_mom;        // [B][Nm][32] completion counters of the moment groups, one per 128-byte line
+    unsigned *cnt_mom;        // [B][DCT_CNT_LINES][32] completion counters (k_combine: of the moment groups,
+                              // [B][Nm][32]; k_dcm: of the blocks), one per 128-byte line
+    int xb = 0;               // k_dcm: cells in x of a block
     int mpw;                  // moments per workgroup (>= 1)
     int b0 = 0;               // the launch covers right-hand sides b0 .. b0 + nb - 1
     int nb = 0;               // (0: all B); B stays the stride of every [B] array
@@ -533,10 +536,12 @@ hipError_t launch_aa(const AAArgs &a, int is_f64, hipStream_t s);
 // first = 1: only the sources at the first iteration of a group, whose q the
 // kernel forms from ext alone (its first source and the M map)
 // max_wg > 0: at most that many (persistent) workgroups, each taking several
-// slabs in turn
+// blocks in turn
 hipError_t launch_dcm(const CombArgs &a, const MapArgs &m, int is_f64, hipStream_t s, int first = 0,
                       int max_wg = 0);
-size_t dcm_lds_bytes(const CombArgs &a, const MapArgs &m, int is_f64);   // Q = ext in the class layouts after a transition
+size_t dcm_lds_bytes(const CombArgs &a, const MapArgs &m, int is_f64, int xb);
+// its block (CombArgs::xb) on a device of lds bytes per workgroup, 0 where it does not apply
+int dcm_block(const CombArgs &a, const MapArgs &m, int is_f64, size_t lds);
 hipError_t launch_mmap(const MapArgs &a, int mode, hipStream_t s);   // mode 0 f64, 1 f32, 2 bf16
 hipError_t launch_dmap(const MapArgs &a, int mode, hipStream_t s);
 hipError_t launch_sweep(SweepArgs a, int is_f64, hipStream_t s, unsigned seq);

@@ -452,6 +452,14 @@ hipError_t launch_transition(const TransArgs &a, int is_f64, hipStream_t s)
     return hipGetLastError();
 }
 
+// The iteration at hand ends its group whatever its change is (a prescribed
+// count or the cap is reached): the next within-group source is used by no
+// sweep, since the next group starts from its own.
+__device__ inline bool surely_last(const CombArgs &a, const RhsState *st, int g)
+{
+    return st->it + 1 >= (a.fixed_iters ? a.fixed_iters[g] : a.max_iter);
+}
+
 // End of an iteration of right-hand side b (called by the one workgroup
 // that completes it, after every workgroup's eps atomics): relative change
 // of phi_00, the stopping rule, and the move to the next group.
@@ -529,6 +537,7 @@ __global__ __launch_bounds__(256) void k_combine(CombArgs a)
     const int lm_lo = mg * a.mpw, lm_hi = min(Nm, lm_lo + a.mpw);
     const int nslab = a.geo.nz * nslj;
     const bool live = true;
+    const bool more = !surely_last(a, st, g);                 // the next source is needed
     const int k = blockIdx.x / nslj;
     const int j0 = (blockIdx.x % nslj) * 16;
     // even pitch: row jl of the tile is read and written at i = r -+ jl, so
@@ -621,6 +630,7 @@ __global__ __launch_bounds__(256) void k_combine(CombArgs a)
             const int jm = okr ? j % nx : 0;
             const unsigned orot = okr ? (unsigned)row_pos(r, j, k, nx, ny) * TS : DCT_OOB;
             const int rr = okr ? r : 0, jr = okr ? jl : 0;
+            if (!more) break;
             bst(rQA, orot, tile[jr * pitch + rot_row(1, rr, jm, nx)]);
             bst(rQB, orot, tile[jr * pitch + rot_row(0, rr, jm, nx)]);
         }
@@ -723,7 +733,15 @@ __global__ __launch_bounds__(256) void k_combine(CombArgs a)
 // after the transition by the FIRST form of the kernel, which for the sources
 // starting a group lays Q = ext (plus a warm start's self-scatter) into the
 // tile and runs only step 3.
-template <typename T, int NRB, int KC, bool FIRST>
+//
+// A block of whole rows (CLOSED, XB = nx) is closed under the class rotations:
+// nx rotated rows of 16 lanes.  A shorter block takes the XB + 15 rotated rows
+// that pass through it, the lanes outside it masked: (XB + 15) / XB of the
+// matrix work and of the 64-byte pieces read, in return for a tile that fits
+// the LDS where that of whole rows does not (128 x 128 x 32, 16 moments, FP64:
+// 266 KB).  The lines that x neighbours share meet in one L2: the blocks of a
+// slab are dealt to one XCD (workgroups go to the 8 XCDs round robin).
+template <typename T, int NRB, int KC, bool FIRST, bool CLOSED>
 __global__ __launch_bounds__(512) void k_dcm(CombArgs a, MapArgs m)
 {
     constexpr bool first = FIRST;
@@ -737,12 +755,13 @@ __global__ __launch_bounds__(512) void k_dcm(CombArgs a, MapArgs m)
     __shared__ double red[16];
     __shared__ double ssg[DCT_MAXMAT * (DCT_MAXL + 1)];
     const int nx = a.geo.nx, ny = a.geo.ny;
+    const int XB = CLOSED ? nx : a.xb, nxb = CLOSED ? 1 : (nx + XB - 1) / XB;
     const int nslj = (ny + 15) >> 4;
-    const unsigned nsl = (unsigned)(a.geo.nz * nslj);          // slabs of one right-hand side
+    const unsigned nsl = (unsigned)(a.geo.nz * nslj * nxb);    // blocks of one right-hand side
     const unsigned NW = nsl * (unsigned)(a.nb > 0 ? a.nb : a.B);   // items of this launch's right-hand sides
     const long C = a.geo.C;
     const int G = a.G, Nm = a.Nm, L = a.L, N = m.N;
-    const int pitch = (nx | 1) + 1;
+    const int pitch = (XB | 1) + 1;
     // moment stride of the tile: 16 rows plus 4 words, so that the 4 lane
     // groups of an MFMA output (moments 4 apart) fall in different banks
     const int LMS = 16 * pitch + 4;
@@ -770,7 +789,9 @@ __global__ __launch_bounds__(512) void k_dcm(CombArgs a, MapArgs m)
     const bool fast = m.chainK <= 1;
     const int Nc0 = m.Nc[0], Nc1 = m.Nc[1];
     // persistent workgroups (the tables above are loaded once): workgroup h
-    // takes work items h, h + gridDim.x, ...; item -> (right-hand side, slab)
+    // takes work items h, h + gridDim.x, ..., of which the bulk is dealt so that
+    // the blocks of a slab stay on one XCD; item -> (right-hand side, block)
+    const unsigned bulk = CLOSED ? 0u : NW / (8u * (unsigned)nxb) * (8u * (unsigned)nxb);
     for (unsigned lin = blockIdx.x; lin < NW; lin += gridDim.x) {
         // the lane indices pass through an opaque zero, so that the per-lane
         // address arithmetic of the item is formed inside the loop instead of
@@ -780,9 +801,13 @@ __global__ __launch_bounds__(512) void k_dcm(CombArgs a, MapArgs m)
         const int tid = (int)threadIdx.x + lz;
         const int l = tid & 63, col = l & 15, kr = l >> 4;
         const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), nwv = blockDim.x >> 6;
-        const unsigned W = lin;
+        unsigned W = lin;
+        if (!CLOSED && lin < bulk) {
+            const unsigned xcd = lin & 7, slot = lin >> 3;
+            W = (unsigned)nxb * ((slot / nxb) * 8 + xcd) + slot % nxb;
+        }
         const int bl = __builtin_amdgcn_readfirstlane((int)(W / nsl));
-        const int slab = __builtin_amdgcn_readfirstlane((int)(W - (unsigned)bl * nsl));
+        const int item = __builtin_amdgcn_readfirstlane((int)(W - (unsigned)bl * nsl));
         const int b = a.b0 + bl;
         RhsState *st = a.state + b;
         if (st->finished) continue;
@@ -790,7 +815,10 @@ __global__ __launch_bounds__(512) void k_dcm(CombArgs a, MapArgs m)
         if (first && (st->pending || st->it != 0)) continue;
         const int gseq = __builtin_amdgcn_readfirstlane(st->g);   // wave-uniform: the buffer descriptors below stay scalar
         const int g = __builtin_amdgcn_readfirstlane(eff_group(gseq, a.G, a.reverse));
+        const bool more = first || !surely_last(a, st, g);
+        const int slab = CLOSED ? item : item / nxb, x0 = CLOSED ? 0 : (item - slab * nxb) * XB;
         const int k = slab / nslj, j0 = (slab % nslj) * 16;
+        const int xw = CLOSED ? nx : min(XB, nx - x0);            // cells in x of this block
         if ((int)threadIdx.x < a.M * (L + 1)) {
             const int mm = threadIdx.x / (L + 1), ll = threadIdx.x - mm * (L + 1);
             ssg[threadIdx.x] = a.ss[(((long)mm * (L + 1) + ll) * G + g) * G + g];
@@ -802,6 +830,21 @@ __global__ __launch_bounds__(512) void k_dcm(CombArgs a, MapArgs m)
         const int jm = jc % nx;
         const int jw = tile_w(j0, ny);                            // elements of a row of the slab
         const int slab0 = k * nx * ny + j0 * nx + (jc - j0);      // this lane's element of row 0 (C < 2^28)
+        // rotated rows of the block: index v of class c -> its row, and the x
+        // within the block of this lane's cell there, or -1 outside the block
+        const int NV = CLOSED ? nx : xw + 15;
+        const int rb0 = CLOSED ? 0 : ((x0 - j0 - 15) % nx + nx) % nx, ra0 = CLOSED ? 0 : (x0 + j0) % nx;
+        auto row_at = [&](int c, int v, int &xi) __attribute__((always_inline)) {
+            if (CLOSED) {
+                xi = jok ? (c == 0 ? (v - jm + nx) % nx : (v + jm) % nx) : -1;
+                return v;
+            }
+            const int x = c == 0 ? v - col : v - 15 + col;
+            xi = jok && (unsigned)x < (unsigned)xw ? x : -1;
+            int r = (c == 0 ? ra0 : rb0) + v;
+            while (r >= nx) r -= nx;
+            return r;
+        };
         // ---- 1. D map of each class into the natural tile.  A wave takes two
         // rows at a time and loads the psi operands of its next pair (the first
         // pair of class B after the last of class A) before the matrix-core work
@@ -818,19 +861,21 @@ __global__ __launch_bounds__(512) void k_dcm(CombArgs a, MapArgs m)
                 for (int u = 0; u < KC; ++u) o[u] = co[min(4 * u + kr, Nc - 1)];
     #pragma unroll
                 for (int h = 0; h < 2; ++h) {
-                    const int r = min(r0 + h * nwv, nx - 1);
+                    int xi;
+                    const int r = row_at(c, min(r0 + h * nwv, NV - 1), xi);
                     const unsigned p4 = (unsigned)(slab0 + r * jw) * (unsigned)sizeof(T);
     #pragma unroll
-                    for (int u = 0; u < KC; ++u) bv[h][u] = bld<T>(rps, o[u] + p4);
+                    for (int u = 0; u < KC; ++u) bv[h][u] = bld<T>(rps, CLOSED || xi >= 0 ? o[u] + p4 : DCT_OOB);
                 }
                 return;
             }
             const int *cd = cds + c * N;
     #pragma unroll
             for (int h = 0; h < 2; ++h) {
-                const int r = min(r0 + h * nwv, nx - 1);
+                int xi;
+                const int r = row_at(c, min(r0 + h * nwv, NV - 1), xi);
                 const long p = slab0 + r * jw;
-                const CellKJI cc{k, jc, c == 0 ? (r - jm + nx) % nx : (r + jm) % nx};
+                const CellKJI cc{k, jc, x0 + max(xi, 0)};
     #pragma unroll
                 for (int u = 0; u < KC; ++u) bv[h][u] = psi[dir_elem(m, c, cd[min(4 * u + kr, Nc - 1)], p, cc)];
             }
@@ -838,18 +883,18 @@ __global__ __launch_bounds__(512) void k_dcm(CombArgs a, MapArgs m)
         bool have = false;                                        // bA holds the operands of the pair at hand
         for (int c = 0; c < (first ? 0 : 2); ++c) {
             const int Nc = c == 0 ? Nc0 : Nc1;
-            if (!have && wv < nx) {
+            if (!have && wv < NV) {
                 load_pair(c, wv, bA);
                 have = true;
             }
-            for (int r0 = wv; r0 < nx; r0 += 2 * nwv) {
+            for (int r0 = wv; r0 < NV; r0 += 2 * nwv) {
                 // operands of the next pair: this class's, or class B's first
                 int rn = r0 + 2 * nwv, cn = c;
-                if (rn >= nx && c == 0) {
+                if (rn >= NV && c == 0) {
                     rn = wv;
                     cn = 1;
                 }
-                const bool next = rn < nx;
+                const bool next = rn < NV;
                 if (next) load_pair(cn, rn, bB);
                 A4 acc[2][NRB];
     #pragma unroll
@@ -868,16 +913,16 @@ __global__ __launch_bounds__(512) void k_dcm(CombArgs a, MapArgs m)
                     }
     #pragma unroll
                 for (int h = 0; h < 2; ++h) {
-                    const int r = r0 + h * nwv;
-                    if (jok && r < nx) {
-                        const int i = c == 0 ? (r - jm + nx) % nx : (r + jm) % nx;   // natural x of (r, j)
+                    int xi;
+                    row_at(c, min(r0 + h * nwv, NV - 1), xi);
+                    if (xi >= 0 && r0 + h * nwv < NV) {
     #pragma unroll
                         for (int rb = 0; rb < NRB; ++rb)
     #pragma unroll
                             for (int e = 0; e < 4; ++e) {
                                 const int lm = rb * 16 + out_row<T>(kr, e);
                                 if (lm < Nm) {
-                                    T *tp = &tile[lm * LMS + col * pitch + i];
+                                    T *tp = &tile[lm * LMS + col * pitch + xi];
                                     *tp = c == 0 ? acc[h][rb][e] : *tp + acc[h][rb][e];
                                 }
                             }
@@ -891,13 +936,13 @@ __global__ __launch_bounds__(512) void k_dcm(CombArgs a, MapArgs m)
             }
             __syncthreads();
         }
-        // ---- 2. combine in natural order: a thread takes one voxel of the slab at
+        // ---- 2. combine in natural order: a thread takes one voxel of the block at
         // a time (material, density and the old phi_00 read once) and all its
         // moments, with the group source of every moment requested up front
         double dmax = 0.0, fmax_ = 0.0;
         T *phib = (T *)a.phi_all + ((long)b * G + g) * Nm * C;
         const T *ext = (const T *)a.ext + (long)b * Nm * C;
-        const int tile_n = 16 * nx;
+        const int tile_n = 16 * xw;
         // ext and phi of this source and group through buffer descriptors: the
         // voxel's byte offset per lane, the moment's (lm C sizeof(T), below 2^31
         // by a host check) as a scalar
@@ -908,9 +953,9 @@ __global__ __launch_bounds__(512) void k_dcm(CombArgs a, MapArgs m)
         // within-group scatter of the moments a warm start begins from), laid
         // into the tile as k_transition forms it
         for (int idx = threadIdx.x; first && idx < tile_n; idx += blockDim.x) {
-            const int jl = idx / nx, i = idx - jl * nx, jy = j0 + jl;
+            const int jl = idx / xw, i = idx - jl * xw, jy = j0 + jl;
             if (jy >= ny) continue;
-            const int v = i + nx * (jy + ny * k);
+            const int v = x0 + i + nx * (jy + ny * k);
             const unsigned v4 = (unsigned)v * (unsigned)sizeof(T);
             const double rh = a.rho[v];
             const int mt = a.mat[v];
@@ -934,9 +979,9 @@ __global__ __launch_bounds__(512) void k_dcm(CombArgs a, MapArgs m)
             }
         }
         for (int idx = threadIdx.x; !first && idx < tile_n; idx += blockDim.x) {
-            const int jl = idx / nx, i = idx - jl * nx, jy = j0 + jl;
+            const int jl = idx / xw, i = idx - jl * xw, jy = j0 + jl;
             if (jy >= ny) continue;
-            const int v = i + nx * (jy + ny * k);
+            const int v = x0 + i + nx * (jy + ny * k);
             const unsigned v4 = (unsigned)v * (unsigned)sizeof(T);
             const double rh = a.rho[v];
             const int mt = a.mat[v];
@@ -961,10 +1006,11 @@ __global__ __launch_bounds__(512) void k_dcm(CombArgs a, MapArgs m)
             }
         }
         __syncthreads();
-        // ---- 3. M map of each class from the tile
+        // ---- 3. M map of each class from the tile (not where its q is that of
+        // no sweep: of 12 prescribed iterations a group one in 12)
         T *q = (T *)m.q + (long)b * N * C;
         const int NS = (Nm + 3) / 4;                              // K-steps of 4 moments
-        if (fast) {
+        if (fast && more) {
             // q stored through a buffer descriptor: every lane stores, rows past
             // the class's directions or the grid take an out-of-range offset
             const rsrc_t rqq = mk_rsrc(wave_ptr(q), (long)N * C * (long)sizeof(T));
@@ -979,8 +1025,9 @@ __global__ __launch_bounds__(512) void k_dcm(CombArgs a, MapArgs m)
                         const int nl = rb * 16 + out_row<T>(kr, e);
                         qo[rb][e] = (nl < Nc && jok) ? co[nl] : DCT_OOB;
                     }
-                for (int r = wv; r < nx; r += nwv) {
-                    const int i = c == 0 ? (r - jm + nx) % nx : (r + jm) % nx;
+                for (int v = wv; v < NV; v += nwv) {
+                    int xi;
+                    const int r = row_at(c, v, xi), i = max(xi, 0);
                     const unsigned p4 = (unsigned)(slab0 + r * jw) * (unsigned)sizeof(T);
                     T bq[4 * NRB];
     #pragma unroll
@@ -993,18 +1040,20 @@ __global__ __launch_bounds__(512) void k_dcm(CombArgs a, MapArgs m)
                         for (int s = 0; s < 4 * NRB; ++s)
                             if (s < NS) acc = mfma_k4(Mt[(c * NcP + rb * 16 + col) * MST + 4 * s + kr], bq[s], acc);
     #pragma unroll
-                        for (int e = 0; e < 4; ++e) bst(rqq, qo[rb][e] == DCT_OOB ? DCT_OOB : qo[rb][e] + p4, acc[e]);
+                        for (int e = 0; e < 4; ++e)
+                            bst(rqq, qo[rb][e] == DCT_OOB || (!CLOSED && xi < 0) ? DCT_OOB : qo[rb][e] + p4, acc[e]);
                     }
                 }
             }
         }
-        for (int c = 0; c < (fast ? 0 : 2); ++c) {
+        for (int c = 0; c < (fast || !more ? 0 : 2); ++c) {
             const int Nc = c == 0 ? Nc0 : Nc1;
             const int *cd = cds + c * N;
-            for (int r = wv; r < nx; r += nwv) {
+            for (int v = wv; v < NV; v += nwv) {
+                int xi;
+                const int r = row_at(c, v, xi), i = max(xi, 0);
                 const long p = slab0 + r * jw;
-                const int i = c == 0 ? (r - jm + nx) % nx : (r + jm) % nx;
-                const CellKJI cc{k, jc, i};
+                const CellKJI cc{k, jc, x0 + i};
                 T bq[4 * NRB];
     #pragma unroll
                 for (int s = 0; s < 4 * NRB; ++s) bq[s] = tile[min(4 * s + kr, Nm - 1) * LMS + col * pitch + i];
@@ -1016,7 +1065,7 @@ __global__ __launch_bounds__(512) void k_dcm(CombArgs a, MapArgs m)
     #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         const int nl = rb * 16 + out_row<T>(kr, e);
-                        if (nl < Nc && jok) q[dir_elem(m, c, cd[nl], p, cc)] = acc[e];
+                        if (nl < Nc && xi >= 0) q[dir_elem(m, c, cd[nl], p, cc)] = acc[e];
                     }
                 }
             }
@@ -1028,7 +1077,7 @@ __global__ __launch_bounds__(512) void k_dcm(CombArgs a, MapArgs m)
             if (threadIdx.x == 0) {
                 atomicMax(&st->eps_num, (unsigned long long)__double_as_longlong(dm));
                 atomicMax(&st->eps_den, (unsigned long long)__double_as_longlong(fm));
-                if (last_block(a.cnt_mom + (long)b * DCT_MAXNM * 32, &st->cnt_combine, (unsigned)slab, nsl))
+                if (last_block(a.cnt_mom + (long)b * DCT_CNT_LINES * 32, &st->cnt_combine, (unsigned)item, nsl))
                     close_iteration(a, st, b, gseq, g);
             }
         }
@@ -1036,12 +1085,25 @@ __global__ __launch_bounds__(512) void k_dcm(CombArgs a, MapArgs m)
     }
 }
 
-size_t dcm_lds_bytes(const CombArgs &a, const MapArgs &m, int is_f64)
+size_t dcm_lds_bytes(const CombArgs &a, const MapArgs &m, int is_f64, int xb)
 {
     const size_t ts = is_f64 ? 8 : 4;
-    const size_t pitch = (size_t)((a.geo.nx | 1) + 1);
+    const size_t pitch = (size_t)((xb | 1) + 1);
     return (size_t)a.Nm * (16 * pitch + 4) * ts + (size_t)2 * m.NmP * (m.NcP + 1) * ts +
            (size_t)2 * m.NcP * (m.NmP + 1) * ts + (size_t)4 * m.N * 4;
+}
+
+// Cells in x of a block: whole rows where they fit the LDS, else the longest of
+// 64, 48 and 32 that does (16 would double the matrix work); 0 if none does or
+// there are more blocks than completion counters.
+int dcm_block(const CombArgs &a, const MapArgs &m, int is_f64, size_t lds)
+{
+    const int nx = a.geo.nx;
+    const long per = (long)a.geo.nz * ((a.geo.ny + 15) / 16);
+    for (int xb : {nx, 64, 48, 32})
+        if (xb <= nx && dcm_lds_bytes(a, m, is_f64, xb) + 1024 <= lds)
+            return per * ((nx + xb - 1) / xb) <= 32L * DCT_CNT_LINES ? xb : 0;
+    return 0;
 }
 
 hipError_t launch_dcm(const CombArgs &a, const MapArgs &m, int is_f64, hipStream_t s, int first, int max_wg)
@@ -1049,23 +1111,34 @@ hipError_t launch_dcm(const CombArgs &a, const MapArgs &m, int is_f64, hipStream
     const int nslj = (a.geo.ny + 15) >> 4;
     const int nb = a.nb > 0 ? a.nb : a.B;
     if (a.b0 < 0 || a.b0 + nb > a.B) return hipErrorInvalidValue;
-    const long nw = (long)a.geo.nz * nslj * nb;
+    if (a.xb < 1 || a.xb > a.geo.nx) return hipErrorInvalidValue;
+    const bool closed = a.xb == a.geo.nx;
+    const long nw = (long)a.geo.nz * nslj * ((a.geo.nx + a.xb - 1) / a.xb) * nb;
     const dim3 grid((unsigned)(max_wg > 0 && max_wg < nw ? max_wg : nw));
-    const size_t shm = dcm_lds_bytes(a, m, is_f64);
+    const size_t shm = dcm_lds_bytes(a, m, is_f64, a.xb);
     const int nrb = (a.Nm + 15) / 16;
-#define DCT_DCM(T, R, K, F)                                                                               \
+#define DCT_DCM_C(T, R, K, F, CL)                                                                          \
     do {                                                                                                  \
-        hipError_t e_ = hipFuncSetAttribute((const void *)k_dcm<T, R, K, F>,                               \
+        hipError_t e_ = hipFuncSetAttribute((const void *)k_dcm<T, R, K, F, CL>,                           \
                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);        \
         if (e_ != hipSuccess) return e_;                                                                  \
-        hipLaunchKernelGGL((k_dcm<T, R, K, F>), grid, dim3(512), shm, s, a, m);                            \
+        hipLaunchKernelGGL((k_dcm<T, R, K, F, CL>), grid, dim3(512), shm, s, a, m);                        \
     } while (0)
-    // the first-iteration form has no D map, so one K-step width serves it
+#define DCT_DCM(T, R, K, F)                                                                               \
+    do {                                                                                                  \
+        if (closed) DCT_DCM_C(T, R, K, F, true); else DCT_DCM_C(T, R, K, F, false);                        \
+    } while (0)
+    // the first-iteration form has no D map, so one K-step width serves it; the
+    // others load K steps of every row whether the class has them or not, so
+    // S6 and S8 have their own (24 directions a class: 482 -> 466 us a launch of
+    // 36 sources at 64 x 64 x 16 FP64 with 6 steps for 8)
 #define DCT_DCM_K(T, R)                                                                                   \
     do {                                                                                                  \
         if (first) DCT_DCM(T, R, 4, true);                                                                 \
         else if (kc <= 4) DCT_DCM(T, R, 4, false);                                                         \
+        else if (kc <= 6) DCT_DCM(T, R, 6, false);                                                         \
         else if (kc <= 8) DCT_DCM(T, R, 8, false);                                                         \
+        else if (kc <= 10) DCT_DCM(T, R, 10, false);                                                       \
         else DCT_DCM(T, R, 12, false);                                                                    \
     } while (0)
     const int kc = ((m.Nc[0] > m.Nc[1] ? m.Nc[0] : m.Nc[1]) + 3) / 4;   // K-steps of one class (<= 12)
@@ -1077,6 +1150,7 @@ hipError_t launch_dcm(const CombArgs &a, const MapArgs &m, int is_f64, hipStream
     }
 #undef DCT_DCM_K
 #undef DCT_DCM
+#undef DCT_DCM_C
     return hipGetLastError();
 }
 

@@ -780,7 +780,7 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
     HC(dbuf(ctx, "leak", leak_max, &d_leak));
     HC(dbuf(ctx, "state", (size_t)B * sizeof(RhsState), &d_state));
     void *d_ccnt;
-    HC(dbuf(ctx, "ccnt", (size_t)B * DCT_MAXNM * 128, &d_ccnt));
+    HC(dbuf(ctx, "ccnt", (size_t)B * DCT_CNT_LINES * 128, &d_ccnt));
     // transition kernels: completion sub-counters and per-workgroup balance sums
     const int tr_blocks = (int)voxel_blocks(nx, ny, nz), tr_nsub = (tr_blocks + 31) / 32;
     void *d_tsub, *d_pbal;
@@ -901,7 +901,7 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
     HC(hipMemsetAsync(d_eps, 0, (size_t)B * G * 8, s));
     HC(hipMemsetAsync(d_leak, 0, leak_max, s));
     HC(hipMemsetAsync(d_err, 0, 4, s));
-    HC(hipMemsetAsync(d_ccnt, 0, (size_t)B * DCT_MAXNM * 128, s));
+    HC(hipMemsetAsync(d_ccnt, 0, (size_t)B * DCT_CNT_LINES * 128, s));
     HC(hipMemsetAsync(d_tsub, 0, (size_t)B * tr_nsub * 128, s));
 
     Geo geo;
@@ -1334,26 +1334,21 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
         ctx->last_rhs = rhsK;
     }
 
-    // D map, combine and M map as one kernel (k_dcm): FP64 / FP32, the slab
-    // tile and tables within the workgroup's LDS, at most 32 DCT_MAXNM slabs
-    // (completion sub-counters); by default when there are enough slabs to
-    // fill the GPU (one or two workgroups per CU at a time)
-    bool fused = false;
-    int dcm_wg = 0;
-    {
-        const long nslab = (long)nz * ((ny + 15) / 16);
-        const size_t lds = dcm_lds_bytes(cb, ma, is64) + 1024;
-        const bool fuse_ok = mode <= 1 && lds <= ctx->lds_max && nslab <= 32L * DCT_MAXNM &&
-                             std::max(pl.Nc[0], pl.Nc[1]) <= 48 &&   // one round of psi loads per class
-                             (size_t)std::max(N, Nm) * C * ts < ((size_t)1 << 31);   // 32-bit offsets of one
-                                                                                      // source's q, psi, ext, phi
-        // by default: at least one slab per CU (measured: 36 sources FP64 220
-        // against 302 ms, the 128x128x32 abdomen FP32 98 against 109 ms)
-        fused = fuse_ok && aam == 0 && (o.fuse_maps > 0 || (o.fuse_maps == 0 && nslab * B >= ctx->ncu));
-        ma.first_only = fused ? 1 : 0;
-        // persistent workgroups: as many as fit the device at once
-        dcm_wg = (2 * lds <= ctx->lds_max ? 2 : 1) * ctx->ncu;
-    }
+    // D map, combine and M map as one kernel (k_dcm): FP64 / FP32, a block's
+    // tile and the tables within the workgroup's LDS, the directions of a class
+    // within one round of loads, 32-bit offsets of one source's q, psi, ext and
+    // phi; by default when there are enough blocks to fill the GPU (one or two
+    // workgroups per CU at a time; measured: 36 sources FP64 220 against 302 ms,
+    // the 128 x 128 x 32 abdomen FP32 98 against 109 ms, FP64 184 us in
+    // x blocks against 290 for the three kernels)
+    cb.xb = mode <= 1 ? dcm_block(cb, ma, is64, ctx->lds_max) : 0;
+    const bool fuse_ok = cb.xb > 0 && std::max(pl.Nc[0], pl.Nc[1]) <= 48 &&
+                         (size_t)std::max(N, Nm) * C * ts < ((size_t)1 << 31);
+    const long nblocks = (long)nz * ((ny + 15) / 16) * (cb.xb > 0 ? (nx + cb.xb - 1) / cb.xb : 0) * B;
+    const bool fused = fuse_ok && aam == 0 && (o.fuse_maps > 0 || (o.fuse_maps == 0 && nblocks >= ctx->ncu));
+    ma.first_only = fused ? 1 : 0;
+    // persistent workgroups: as many as fit the device at once
+    const int dcm_wg = (fused && 2 * (dcm_lds_bytes(cb, ma, is64, cb.xb) + 1024) <= ctx->lds_max ? 2 : 1) * ctx->ncu;
     ctx->last_fused = fused;
     ctx->last_warm = warm;
 
@@ -1962,7 +1957,7 @@ static int adjoint_common(dct_ctx *ctx, const double *roi, const dct_opts *opts,
     HC(hipMemsetAsync(d_ait, 0, (size_t)B * G * 4, s));
     HC(hipMemsetAsync(d_aeps, 0, (size_t)B * G * 8, s));
     HC(hipMemsetAsync(B_("err"), 0, 4, s));
-    HC(hipMemsetAsync(B_("ccnt"), 0, (size_t)B * DCT_MAXNM * 128, s));
+    HC(hipMemsetAsync(B_("ccnt"), 0, (size_t)B * DCT_CNT_LINES * 128, s));
     const int tr_nsub = (int)((voxel_blocks(nx, ny, nz) + 31) / 32);
     HC(hipMemsetAsync(B_("tsub"), 0, (size_t)B * tr_nsub * 128, s));
     HC(launch_adj_init(C, G, B, (const uint8_t *)B_("mat"), (const double *)B_("kap"), (const double *)d_roi,
