@@ -451,8 +451,9 @@ struct SweepArgs {
     const void *sigch;        // T [2][G][K C] sigma_t in the chain layout of period K nx
     int b0 = 0;               // the launch covers right-hand sides b0 .. b0 + nb - 1 (layered
     int nb = 0;               // waves and chained sources; 0: all B); B stays the stride of every [B] array
-    int tS = 0;               // > 0: tile waves, this many y streams (k_sweep_t; whole y and z extent
-                              //      in one workgroup, nblk = 1)
+    int tS = 0;               // > 0: tile waves, this many y streams (k_sweep_t; the whole y extent in
+    int tK = 0;               //      one workgroup, and tK tiles of 4 layers; nblk = the z groups)
+    void *tface = nullptr;    // T [B][N][nblk - 1][ceil(ny / 16)][nx][16] z faces between the groups
     int rhsK;                 // > 1: one direction of up to rhsK unfinished right-hand sides per
                               //      workgroup, swept back to back (k_sweep_rc)
 };
@@ -545,8 +546,12 @@ int dcm_block(const CombArgs &a, const MapArgs &m, int is_f64, size_t lds);
 hipError_t launch_mmap(const MapArgs &a, int mode, hipStream_t s);   // mode 0 f64, 1 f32, 2 bf16
 hipError_t launch_dmap(const MapArgs &a, int mode, hipStream_t s);
 hipError_t launch_sweep(SweepArgs a, int is_f64, hipStream_t s, unsigned seq);
-// y streams of a tile-wave sweep (SweepArgs::tS), 0 where it does not apply
-int tile_streams(int nx, int ny, int nz, long nwg, int is_f64, int ncu, size_t lds);
+// y streams and layer tiles per workgroup of a tile-wave sweep (SweepArgs::tS, tK),
+// S = 0 where it does not apply
+struct TilePlan {
+    int S, K;
+};
+TilePlan tile_plan(int nx, int ny, int nz, long nwg, int is_f64, int ncu, size_t lds);
 hipError_t launch_dose(const DoseArgs &a, int is_f64, hipStream_t s);
 // sum_v w[v] x[v] (FP64, fixed order) into part[nb], nb = min(1024, ceil(n / 256));
 // part needs nb + 1 entries

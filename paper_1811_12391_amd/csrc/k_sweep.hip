@@ -811,16 +811,16 @@ __host__ __device__ inline int tile_period(int nx, int S, int NJ)
 // Slots of a y-face ring: a tile and what lanes write past its end.
 __host__ __device__ inline int tile_yslots(int P) { return P + 32; }
 // LDS words (of T) of a tile-wave workgroup: a pad that keeps every ring
-// address positive, the ring of boundary values and one z-face ring per wave,
-// [2 BG][64] each, the y-face rings [S][NK][slots][4], those of the grid's last
+// address positive, the ring of boundary values and one z-face ring per wave
+// (in z groups, then one per stream for the faces handed in), [2 BG][64] each, the y-face rings [S][NK][slots][4], those of the grid's last
 // row [NK][slots][4], and a place for what no one reads.
-__host__ __device__ inline long tile_ring_words(int S, int NK)
+__host__ __device__ inline long tile_ring_words(int S, int NK, bool groups)
 {
-    return (DCT_TILE_BG - 1) * 64 + (long)(1 + S * NK) * 2 * DCT_TILE_BG * 64;
+    return (DCT_TILE_BG - 1) * 64 + (long)(1 + S * NK + (groups ? S : 0)) * 2 * DCT_TILE_BG * 64;
 }
-__host__ __device__ inline long tile_lds_words(int S, int NK, int P)
+__host__ __device__ inline long tile_lds_words(int S, int NK, int P, bool groups)
 {
-    return tile_ring_words(S, NK) + (long)(S + 1) * NK * tile_yslots(P) * 4 + 64 * 4 + 4 * DCT_TILE_BG;
+    return tile_ring_words(S, NK, groups) + (long)(S + 1) * NK * tile_yslots(P) * 4 + 64 * 4 + 4 * DCT_TILE_BG;
 }
 
 // Tile waves (every z layer and y row of a direction in one workgroup): a wave
@@ -865,7 +865,20 @@ __host__ __device__ inline long tile_lds_words(int S, int NK, int P)
 //
 // Every cell's arithmetic is that of k_sweep, so the results are the same bit
 // for bit.  MODE as in k_sweep; FIX: the set-to-zero fixup is on.
-template <typename T, int PF, int MODE, bool FIX>
+//
+// ZG: the layers of a direction are split into z groups of tK tiles, one
+// workgroup each (blockIdx.z in sweep order), all in one launch, so that a few
+// directions still reach most CUs with waves that have a SIMD nearly to
+// themselves.  The z faces between groups go through memory as in k_sweep's
+// pipelined blocks: workgroups of a direction share an XCD (the item index is
+// padded to a multiple of 8) and come in sweep order, an element is stored by
+// the group below, waited for (bounded) until it is no longer the empty marker,
+// and emptied again.  One extra wave per workgroup does all of it, 4 steps x 16
+// rows at a time: it plays the wave below the first (ring 1 + S NK + s in place
+// of the zero ring), reading a group of steps ahead, and stores what the top
+// waves left in their rings; the sweeping waves run the same code as without
+// groups, and wait for it at the barrier.
+template <typename T, int PF, int MODE, bool FIX, bool ZG>
 __global__ __launch_bounds__(1024) void k_sweep_t(SweepArgs a)
 {
     constexpr bool ADJ = MODE == 2, KEEP = MODE == 1;
@@ -877,7 +890,9 @@ __global__ __launch_bounds__(1024) void k_sweep_t(SweepArgs a)
     static_assert(PF + BG + DCT_TILE_SKEW <= DCT_TILE_XMIN, "the next tile is set up before a lane starts it");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_t[];
     __shared__ double red[3][16];
-    const int b = a.b0 + (int)blockIdx.y, n = (int)blockIdx.x;
+    const int bl = ZG ? (int)blockIdx.x / a.N : (int)blockIdx.y;
+    const int b = a.b0 + bl, n = (int)blockIdx.x - (ZG ? bl * a.N : 0);
+    if (ZG && bl >= (a.nb > 0 ? a.nb : a.B)) return;
     const long item = (long)b * a.N + n;
     if (a.state[b].finished) return;
     const int g = eff_group(a.state[b].g, a.G, a.reverse);
@@ -885,7 +900,7 @@ __global__ __launch_bounds__(1024) void k_sweep_t(SweepArgs a)
     const long C = a.C;
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l = lane & 15, kl = lane >> 4;
-    const int NK = (nz + 3) >> 2, NJ = (ny + 15) >> 4, S = a.tS;
+    const int NKT = (nz + 3) >> 2, NK = ZG ? a.tK : NKT, zg = ZG ? (int)blockIdx.z : 0, NJ = (ny + 15) >> 4, S = a.tS;
     int s = 0, kt = wv;                                      // wave (s, kt)
     while (kt >= NK) {
         kt -= NK;
@@ -908,7 +923,7 @@ __global__ __launch_bounds__(1024) void k_sweep_t(SweepArgs a)
     const rsrc_t rsg = mk_rsrc((const T *)a.sigc + ((long)cls * a.G + g) * C, C * TS);
     // layers of this wave: a partial tile that comes first (sz < 0) fills the
     // upper lanes, as in y below
-    const int K = sz ? kt : NK - 1 - kt, wz = min(4, nz - 4 * K);
+    const int ktg = zg * NK + kt, K = sz ? ktg : NKT - 1 - ktg, wz = ktg < NKT ? min(4, nz - 4 * K) : 0;
     const int kloc = sz ? kl : 3 - kl;
     const bool kok = kloc < wz;
     const int dr = sx ? 1 : -1, i0 = sx ? 0 : nx - 1;
@@ -916,10 +931,10 @@ __global__ __launch_bounds__(1024) void k_sweep_t(SweepArgs a)
     const int eph = skew + nx >= P ? skew + nx - P : skew + nx;   // phase at which the lane's row has ended
 
     T *zr = (T *)smem_t + (BG - 1) * 64;                     // [1 + S NK][RS][64]
-    T *yf = (T *)smem_t + tile_ring_words(S, NK);            // [S + 1][NK][M][4]
+    T *yf = (T *)smem_t + tile_ring_words(S, NK, ZG);        // [S + 1][NK][M][4]
     {
         // every face starts as the vacuum boundary value
-        const int nw = (int)(tile_lds_words(S, NK, P) * (long)TS / 16);
+        const int nw = (int)(tile_lds_words(S, NK, P, ZG) * (long)TS / 16);
         for (int i = threadIdx.x; i < nw; i += blockDim.x) ((uint4 *)smem_t)[i] = uint4{0u, 0u, 0u, 0u};
     }
     // y faces: at its step tau the wave's last row writes slot tau mod M of the
@@ -943,7 +958,7 @@ __global__ __launch_bounds__(1024) void k_sweep_t(SweepArgs a)
     // step t - 1, slot (u - 1) mod RS; kl = 0 the top row of the wave below (or
     // the boundary ring) of step t - BG, slot (u - BG) mod RS, which is BG + 1
     // slots above for u in [1, BG) and BG - 1 below otherwise
-    const T *zn = zr + (kt == 0 ? 0 : wv) * RS * 64 + 48 + l;
+    const T *zn = zr + (kt == 0 ? (ZG && zg > 0 ? 1 + S * NK + s : 0) : wv) * RS * 64 + 48 + l;
     const T *zp = kl > 0 ? zw - 16 : zn + (BG + 1) * 64;
     const T *zm = kl > 0 ? zw - 16 : zn - (BG - 1) * 64;
 
@@ -992,7 +1007,7 @@ __global__ __launch_bounds__(1024) void k_sweep_t(SweepArgs a)
                        NJ > S && slast < S - 1 ? (S - 1) * DCT_TILE_LY + ((NJ - 1) / S - 1) * P : 0) +
                    (NK - 1) * LZ + nx + DCT_TILE_SKEW + 1;
     // the lane's z outflow leaves the grid: its layer is the last in sweep order
-    const T zone = kt == NK - 1 && kl == (sz ? wz - 1 : 3) ? (T)1 : (T)0;
+    const T zone = ktg == NKT - 1 && kl == (sz ? wz - 1 : 3) ? (T)1 : (T)0;
 
     T qr[PF], sr[PF];
     unsigned offr[PF];
@@ -1013,6 +1028,68 @@ __global__ __launch_bounds__(1024) void k_sweep_t(SweepArgs a)
     double lx = 0.0, lz = 0.0;
     const bool whole = P > nx + DCT_TILE_SKEW;               // every row of a tile ends before the next tile starts
     __syncthreads();
+    if (ZG && wv == S * NK) {
+        // the wave of the handed-over faces: element (tile in sweep order, x, l)
+        // of the boundary below (in) and above (out) this group
+        const long nf = (long)NJ * nx * 16;
+        T *fb = (T *)a.tface + (item * (a.nblk - 1) + zg) * nf;
+        const bool cons = zg > 0, prod = zg < a.nblk - 1;
+        const rsrc_t rin = mk_rsrc(cons ? fb - nf : nullptr, cons ? nf * TS : 0L);
+        const rsrc_t rout = mk_rsrc(prod ? fb : nullptr, prod ? nf * TS : 0L);
+        const float ip = 1.0f / (float)P;
+        int spins = 0;
+        // byte offset of the element that a lane of row l, starting at step st
+        // of its tiles, takes at step t; none between rows and for short tiles
+        auto where = [&](int q, int t, int st) __attribute__((always_inline)) {
+            const int xi = t - st - l;
+            int m = (int)((float)xi * ip);
+            m = m * P > xi ? m - 1 : ((m + 1) * P <= xi ? m + 1 : m);
+            const int x = xi - m * P, jt = q + m * S, J = sy ? jt : NJ - 1 - jt;
+            const bool ok = xi >= 0 && x < nx && jt < NJ && (sy ? l : 15 - l) < ny - 16 * J;
+            return ok ? (unsigned)((jt * nx + x) * 16 + l) * TS : DCT_OOB;
+        };
+        auto give = [&](int t) __attribute__((always_inline)) {
+            // what the top waves left in their rings in the BG steps before t
+            if (!prod) return;
+            for (int q = 0; q < S; ++q) {
+                const int tau = t - BG + kl;
+                const T v = zr[((1 + q * NK + NK - 1) * RS + (tau & (RS - 1))) * 64 + 48 + l];
+                bst_dev(rout, where(q, tau, q * DCT_TILE_LY + (NK - 1) * LZ + 6), v);
+            }
+        };
+        T v[4] = {(T)0, (T)0, (T)0, (T)0};
+        if (cons)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (q < S) v[q] = bld_dev<T>(rin, where(q, -U + kl + BG + 1, q * DCT_TILE_LY));
+        for (int tb = -U; tb < NT; tb += U)
+#pragma unroll 1
+            for (int gq = 0; gq < U / BG; ++gq) {
+                const int t = tb + BG * gq;
+                give(t);
+                if (cons) {
+                    // step tau = t + kl of the wave below: used at tau + BG + 1
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        if (q >= S) break;
+                        const unsigned o = where(q, t + kl + BG + 1, q * DCT_TILE_LY);
+                        while (__builtin_amdgcn_ballot_w64(is_empty(v[q])) != 0 && spins < DCT_SPIN_LIMIT) {
+                            __builtin_amdgcn_s_sleep(1);
+                            ++spins;
+                            v[q] = bld_dev<T>(rin, o);
+                        }
+                        zr[((1 + S * NK + q) * RS + ((t + kl) & (RS - 1))) * 64 + 48 + l] = v[q];
+                        bst_dev(rin, o, face_empty<T>());
+                        v[q] = bld_dev<T>(rin, where(q, t + kl + 2 * BG + 1, q * DCT_TILE_LY));
+                    }
+                }
+                __syncthreads();
+            }
+        give(((NT + U - 1) / U) * U);
+        if (spins >= DCT_SPIN_LIMIT && lane == 0) atomicOr(a.err, 1);
+        __syncthreads();
+        return;
+    }
 
     int tb = -U;
     for (; tb + U <= t0 - PF; tb += U)
@@ -1158,7 +1235,7 @@ __global__ __launch_bounds__(1024) void k_sweep_t(SweepArgs a)
     if (threadIdx.x < 3) {
         double sum = 0.0;
         for (int q = 0; q < S * NK; ++q) sum += red[threadIdx.x][q];
-        a.leak_part[item * a.nblk * 3 + threadIdx.x] = sum;
+        a.leak_part[(item * a.nblk + zg) * 3 + threadIdx.x] = sum;
     }
 }
 
@@ -1636,23 +1713,39 @@ __global__ __launch_bounds__(1024 / ZL) void k_sweep_rc(SweepArgs a)
     }
 }
 
-// Streams of a tile-wave launch over nwg directions of an nx x ny x nz grid on
-// a device of ncu compute units and lds bytes per workgroup; 0: the grid needs
-// another schedule.  One stream costs the fewest wave-steps, so it is taken
-// once its waves give every SIMD four; below that the steps of a direction
-// count, and its tiles are spread over two streams, or over 8 waves.  (64 x 64
-// x 16, 80 directions: 1 / 2 / 3 / 4 streams 89 / 64.7 / 64.2 / 64.8 us in FP32,
-// 104 / 83 / 86 / 89 in FP64: more waves on a SIMD only take each other's slots.)
-int tile_streams(int nx, int ny, int nz, long nwg, int is_f64, int ncu, size_t lds)
+// Streams and z groups of a tile-wave launch over nwg directions of an nx x ny x
+// nz grid on a device of ncu compute units and lds bytes per workgroup; S = 0:
+// the grid needs another schedule.  One stream costs the fewest wave-steps, so
+// it is taken once its waves give every SIMD four; below that the steps of a
+// direction count, and its tiles are spread over two streams, or over 8 waves
+// (64 x 64 x 16, 80 directions: 1 / 2 / 3 / 4 streams 89 / 64.7 / 64.2 / 64.8 us
+// in FP32, 104 / 83 / 86 / 89 in FP64: more waves on a SIMD only take each
+// other's slots), and its layers over as many CUs as there are (80 directions of
+// 128 x 128 x 32, two streams, FP32 / FP64: one group 255 / 424 us, two of 4 tiles
+// 204 / 331, three 232 / 346, four 239 / 336; 4 streams by 2 tiles 264 / 388; 48 of
+// 256 x 256 x 64 FP32: blocks of k_sweep 1,225, 4 groups 833, 6 groups 811, 3
+// groups 984; 64 x 64 x 16 FP64: one group 79, two of 2 tiles 69, four 76).
+TilePlan tile_plan(int nx, int ny, int nz, long nwg, int is_f64, int ncu, size_t lds)
 {
-    const int NK = (nz + 3) / 4, NJ = (ny + 15) / 16;
-    auto fits = [&](int S) {
-        return S * NK <= 16 && (size_t)tile_lds_words(S, NK, tile_period(nx, S, NJ)) * (is_f64 ? 8 : 4) + 512 <= lds;
+    const int NKT = (nz + 3) / 4, NJ = (ny + 15) / 16;
+    auto fits = [&](int S, int NK) {
+        const bool zgr = NK < NKT;
+        return S * NK + (zgr ? 1 : 0) <= 16 &&
+               (size_t)tile_lds_words(S, NK, tile_period(nx, S, NJ), zgr) * (is_f64 ? 8 : 4) + 512 <= lds;
     };
-    if (!fits(1)) return 0;
+    // z groups of up to 4 tiles while every one of them gets a CU (two at least,
+    // from 16 layers on): each hands its faces on some 20 us behind the one
+    // below, which its waves' shorter steps have to win back
+    const long zcap = std::min<long>(std::max(2, (NKT + 3) / 4), NKT >= 4 ? ncu / std::max(1L, nwg) : 1);
+    if (zcap > 1) {
+        const int K = (NKT + (int)zcap - 1) / (int)zcap;
+        for (int S = std::min(2, NJ); S > 0; --S)
+            if (fits(S, K)) return TilePlan{S, K};
+    }
+    if (!fits(1, NKT)) return TilePlan{0, 0};
     int S = 1;
-    while (S < NJ && fits(S + 1) && (S < 2 || S * NK < 8) && nwg * NK * S < 16L * ncu) ++S;
-    return S;
+    while (S < NJ && fits(S + 1, NKT) && (S < 2 || S * NKT < 8) && nwg * NKT * S < 16L * ncu) ++S;
+    return TilePlan{S, NKT};
 }
 
 hipError_t launch_sweep(SweepArgs a, int is_f64, hipStream_t s, unsigned seq)
@@ -1713,17 +1806,27 @@ hipError_t launch_sweep(SweepArgs a, int is_f64, hipStream_t s, unsigned seq)
         return hipGetLastError();
     }
     if (a.tS > 0) {
-        // tile waves: S x NK waves, the whole y and z extent in one workgroup
-        const int NK = (a.nz + 3) / 4, NJ = (a.ny + 15) / 16;
-        if (a.tS > NJ || a.tS * NK > 16 || a.pipe || a.inflow || a.nblk != 1) return hipErrorInvalidValue;
-        const dim3 tgrid((unsigned)a.N, (unsigned)nb), tblock(64 * a.tS * NK);
-        const size_t shm = (size_t)tile_lds_words(a.tS, NK, tile_period(a.nx, a.tS, NJ)) * (is_f64 ? 8 : 4);
-#define DCT_TILE(T, PF, MD, FX)                                                                          \
+        // tile waves: S x NK waves, the whole y extent and a z group in one workgroup
+        const int NKT = (a.nz + 3) / 4, NK = a.tK > 0 ? a.tK : NKT, NJ = (a.ny + 15) / 16;
+        const int nzg = (NKT + NK - 1) / NK;
+        const bool zgr = nzg > 1;
+        if (a.tS > NJ || a.tS * NK + (zgr ? 1 : 0) > 16 || (zgr && (a.tS > 4 || !a.tface)) || a.pipe || a.inflow ||
+            a.nblk != nzg)
+            return hipErrorInvalidValue;
+        const dim3 tgrid(zgr ? 8u * (unsigned)(((long)a.N * nb + 7) / 8) : (unsigned)a.N, zgr ? 1u : (unsigned)nb,
+                         (unsigned)nzg);
+        const dim3 tblock(64 * (a.tS * NK + (zgr ? 1 : 0)));
+        const size_t shm = (size_t)tile_lds_words(a.tS, NK, tile_period(a.nx, a.tS, NJ), zgr) * (is_f64 ? 8 : 4);
+#define DCT_TILE_Z(T, PF, MD, FX, Z)                                                                     \
     do {                                                                                                 \
-        hipError_t e_ = hipFuncSetAttribute((const void *)k_sweep_t<T, PF, MD, FX>,                       \
+        hipError_t e_ = hipFuncSetAttribute((const void *)k_sweep_t<T, PF, MD, FX, Z>,                    \
                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);       \
         if (e_ != hipSuccess) return e_;                                                                 \
-        hipLaunchKernelGGL((k_sweep_t<T, PF, MD, FX>), tgrid, tblock, shm, s, a);                         \
+        hipLaunchKernelGGL((k_sweep_t<T, PF, MD, FX, Z>), tgrid, tblock, shm, s, a);                      \
+    } while (0)
+#define DCT_TILE(T, PF, MD, FX)                                                                          \
+    do {                                                                                                 \
+        if (zgr) DCT_TILE_Z(T, PF, MD, FX, true); else DCT_TILE_Z(T, PF, MD, FX, false);                  \
     } while (0)
 #define DCT_TILE_M(T, PF)                                                                                \
     do {                                                                                                 \
@@ -1738,6 +1841,7 @@ hipError_t launch_sweep(SweepArgs a, int is_f64, hipStream_t s, unsigned seq)
         else DCT_TILE_M(float, 4);
 #undef DCT_TILE_M
 #undef DCT_TILE
+#undef DCT_TILE_Z
         return hipGetLastError();
     }
     if (layered) {

@@ -158,6 +158,8 @@ struct dct_ctx {
     size_t lds_max = 65536;            // LDS bytes one workgroup may allocate on the device
     int ncu = 256;                     // compute units of the device
     std::string arch;                  // the device's architecture name (tune-cache key)
+    bool tface_clean = false;          // the first tface_bytes of "tface" hold only the empty marker
+    size_t tface_bytes = 0;
     bool pipe_clean = false;           // pipelined-block face buffers hold only the empty marker
     unsigned sweep_seq = 0;            // counts sweep launches (part of the pipelined blocks' launch tag)
     hipStream_t own_stream = nullptr;  // capture stream when the context's stream is the null stream
@@ -776,6 +778,20 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
         if (d_yfp != old_y || d_zfp != old_z) ctx->pipe_clean = false;
         if (d_hint != old_h) HC(hipMemsetAsync(d_hint, 0, (size_t)B * N * pl.NBJ * ((nz + 1) / 2) * 8, s));
     }
+    // z faces between the groups of a tile-wave sweep, empty between launches
+    const TilePlan tile = tile_plan(nx, ny, nz, (long)B * N, is64, ctx->ncu, ctx->lds_max);
+    const int tile_zg = tile.S > 0 ? ((nz + 3) / 4 + tile.K - 1) / tile.K : 1;
+    void *d_tf = nullptr;
+    if (tile_zg > 1) {
+        const size_t tf_bytes = (size_t)B * N * (tile_zg - 1) * ((ny + 15) / 16) * nx * 16 * ts;
+        void *old = ctx->bufs["tface"].p;
+        HC(dbuf(ctx, "tface", tf_bytes, &d_tf));
+        if (d_tf != old || ctx->tface_bytes < tf_bytes || !ctx->tface_clean) {
+            HC(hipMemsetAsync(d_tf, 0xff, tf_bytes, s));
+            ctx->tface_clean = true;
+            ctx->tface_bytes = tf_bytes;
+        }
+    }
     const size_t leak_max = (size_t)B * N * pl.NBJ * nz * 3 * 8;   // any block split (z layers >= 1)
     HC(dbuf(ctx, "leak", leak_max, &d_leak));
     HC(dbuf(ctx, "state", (size_t)B * sizeof(RhsState), &d_state));
@@ -1082,6 +1098,8 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
     sw.hint = (unsigned long long *)d_hint;
     sw.seq = 0;
     sw.err = (int *)d_err;
+    sw.tK = tile.K;
+    sw.tface = d_tf;
 
     CombArgs cb;
     cb.geo = geo;
@@ -1144,15 +1162,14 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
     const bool layered_ok = ny <= 64 && nz <= 16;
     // tile waves (coupling 4): any grid of up to 64 layers whose faces fit the
     // LDS when the schedule is free, the layered waves' grids when asked for
-    const int tile_S = tile_streams(nx, ny, nz, (long)B * N, is64, ctx->ncu, ctx->lds_max);
     const bool free_sched = o.sweep_bk == 0 && o.sweep_sync == 0 && o.sweep_chain <= 1;
-    const bool tile_ok = tile_S > 0 && (free_sched || layered_ok) && !o.test_inflow;
+    const bool tile_ok = tile.S > 0 && (free_sched || layered_ok) && !o.test_inflow;
     auto set_coupling = [&](int cpl) {
-        sw.tS = cpl == 4 && tile_ok ? tile_S : 0;
+        sw.tS = cpl == 4 && tile_ok ? tile.S : 0;
         if (sw.tS > 0) {
-            // one workgroup per direction, whatever the grid
-            pl.NBJ = pl.NBK = pl.nblk = pl.ndiag = 1;
-            sw.NBJ = sw.NBK = sw.nblk = tr.nblk = 1;
+            // one workgroup per direction and z group, whatever the grid
+            pl.NBJ = pl.NBK = pl.ndiag = sw.NBJ = sw.NBK = 1;
+            pl.nblk = sw.nblk = tr.nblk = tile_zg;
         }
         sw.sync = cpl == 1;
         sw.pipe = cpl == 3;
@@ -1283,7 +1300,7 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
                         // a bounded wait gave up: drop this candidate, reset the
                         // flag and the handed-over faces
                         HC(hipMemsetAsync(d_err, 0, 4, s));
-                        ctx->pipe_clean = false;
+                        ctx->pipe_clean = ctx->tface_clean = false;
                         continue;
                     }
                     float ms = 0.0f;
@@ -1554,7 +1571,7 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
     HC(hipMemcpy(&h_err, d_err, 4, hipMemcpyDeviceToHost));
     if (h_err) {
         ctx->solved = false;
-        ctx->pipe_clean = false;
+        ctx->pipe_clean = ctx->tface_clean = false;
         return fail(ctx, DCT_EDEVICE, "solve: a sweep wave wait exceeded its bound (inter-wave synchronisation)");
     }
     int status = DCT_OK;
@@ -2072,10 +2089,13 @@ static int adjoint_common(dct_ctx *ctx, const double *roi, const dct_opts *opts,
     sw.layers = 0;
     // transposed sweeps: tile waves after a tile-wave forward solve, otherwise
     // k_sweep (barrier coupling for layered schedules)
-    sw.tS = ctx->last_sync == 4 ? tile_streams(nx, ny, nz, (long)B * N, is64, ctx->ncu, ctx->lds_max) : 0;
+    const TilePlan tile = tile_plan(nx, ny, nz, (long)B * N, is64, ctx->ncu, ctx->lds_max);
+    sw.tS = ctx->last_sync == 4 ? tile.S : 0;
     if (sw.tS > 0) {
-        pl.NBJ = pl.NBK = pl.nblk = pl.ndiag = 1;
-        sw.NBJ = sw.NBK = sw.nblk = 1;
+        sw.tK = tile.K;
+        sw.tface = B_("tface");
+        pl.NBJ = pl.NBK = pl.ndiag = sw.NBJ = sw.NBK = 1;
+        pl.nblk = sw.nblk = ((nz + 3) / 4 + tile.K - 1) / tile.K;
     }
     sw.chainK = 1;
     sw.rhsK = 1;
@@ -2165,7 +2185,7 @@ static int adjoint_common(dct_ctx *ctx, const double *roi, const dct_opts *opts,
     int h_err = 0;
     HC(hipMemcpy(&h_err, B_("err"), 4, hipMemcpyDeviceToHost));
     if (h_err) {
-        ctx->pipe_clean = false;
+        ctx->pipe_clean = ctx->tface_clean = false;
         return fail(ctx, DCT_EDEVICE, "adjoint: a sweep wave wait exceeded its bound");
     }
     if (unfinished != 0) return fail(ctx, DCT_ENOTCONV, "adjoint: iteration-set cap reached");
