@@ -216,21 +216,27 @@ __device__ inline void wait_own_memory_ops() { asm volatile("s_waitcnt vmcnt(0)"
 // Two-level "last workgroup" detection over the nblk workgroups of one
 // right-hand side: workgroup i counts on sub-counter i / 32 (one 128-byte
 // line each: sub[(i / 32) * 32]), the last of each group of 32 on `top`, so
-// no counter takes an atomic from every workgroup.  True in exactly one
+// no counter takes an atomic from every workgroup (up to 64 count on `top`
+// alone, a round trip less).  True in exactly one
 // workgroup, after the device atomics of every workgroup (issued before its
 // call) are complete; the counters are left at zero.  One thread calls it.
 __device__ inline bool last_block(unsigned *sub, unsigned *top, unsigned i, unsigned nblk)
 {
     wait_own_memory_ops();
+    // (the counters' resets are waited for by nobody: their next use is a later
+    // kernel's)
+    if (nblk <= 64) {
+        if (atomicAdd(top, 1u) != nblk - 1) return false;
+        atomicExch(top, 0u);
+        return true;
+    }
     const unsigned grp = i >> 5, ngrp = (nblk + 31) >> 5;
     const unsigned in_grp = nblk - (grp << 5) < 32u ? nblk - (grp << 5) : 32u;
     unsigned *c = sub + grp * 32;
     if (atomicAdd(c, 1u) != in_grp - 1) return false;
     atomicExch(c, 0u);
-    wait_own_memory_ops();
     if (atomicAdd(top, 1u) != ngrp - 1) return false;
     atomicExch(top, 0u);
-    wait_own_memory_ops();
     return true;
 }
 
@@ -353,6 +359,7 @@ struct CombArgs {
     unsigned *cnt_mom;        // [B][DCT_CNT_LINES][32] completion counters (k_combine: of the moment groups,
                               // [B][Nm][32]; k_dcm: of the blocks), one per 128-byte line
     int xb = 0;               // k_dcm: cells in x of a block
+    int *n_unfinished = nullptr;   // set: a non-finite change finishes its source at once (no transition follows)
     int mpw;                  // moments per workgroup (>= 1)
     int b0 = 0;               // the launch covers right-hand sides b0 .. b0 + nb - 1
     int nb = 0;               // (0: all B); B stays the stride of every [B] array
