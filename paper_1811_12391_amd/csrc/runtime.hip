@@ -1209,9 +1209,11 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
         int bk = o.sweep_bk > 0 ? o.sweep_bk : 16;
         // untuned: tile waves, except that with a CU to itself for every
         // direction of a one-block grid the barrier coupling's fewer steps are
-        // faster (24 x 24 x 8, 24 directions, FP64: 26 against 34 us a sweep)
+        // faster in FP32 and on up to 8 layers (us an iteration, barrier / tiles:
+        // 24 x 24 x 8 FP64 42.1 / 45.6, 64 x 64 x 16 FP32 93.6 / 97.1, but 61 x 45 x
+        // 13 FP64 120 / 115, 64 x 64 x 16 FP64 136 / 116)
         int cpl = o.sweep_sync > 0 ? o.sweep_sync
-                                   : (!free_sched || !tile_ok ? 1 : (layered_ok && (long)B * N <= ctx->ncu ? 2 : 4));
+                                   : (!free_sched || !tile_ok ? 1 : (layered_ok && (long)B * N <= ctx->ncu && (!is64 || nz <= 8) ? 2 : 4));
         chainK = o.sweep_chain > 1 ? o.sweep_chain :
                  ((cpl >= 6 && cpl <= 8 && !chain_ks.empty()) ? chain_ks.back() : 1);
         rhsK = o.sweep_rhs_chain > 0 ? o.sweep_rhs_chain : std::min(B, 4);
@@ -1372,6 +1374,20 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
     // upper bound of iteration sets: every group at its cap plus one transition each
     long cap_sets = 2;
     for (int g = 0; g < G; ++g) cap_sets += (o.fixed_iters ? o.fixed_iters[g] : o.max_iter) + 1;
+    // with prescribed counts every source starts its groups in sets known here:
+    // the others need no transition and no first form (launches that would find
+    // nothing to do; a captured chunk is replayed anywhere and keeps them).  A
+    // non-finite source is then finished by the iteration that finds it, as no
+    // transition follows.
+    std::vector<long> starts;
+    if (o.fixed_iters && !o.use_graph) {
+        starts.push_back(0);
+        for (int g = 0; g < G; ++g) starts.push_back(starts.back() + o.fixed_iters[g]);
+    }
+    auto starts_group = [&](long set) {
+        return starts.empty() || set > starts.back() || std::binary_search(starts.begin(), starts.end(), set);
+    };
+    cb.n_unfinished = starts.empty() ? nullptr : (int *)d_unf;
     const int chunk = o.chunk > 0 ? o.chunk : 4;
     const bool profile = o.profile && !o.use_graph;
     const int pevery = o.profile > 1 ? o.profile : 1;   // time every pevery-th sweep launch
@@ -1394,7 +1410,7 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
     // chained sources on two streams: a half's launch keeps the chains per
     // direction of a one-stream launch, ceil(B / R), with fewer sources each
     const int rc_nch = sw.rhsK > 1 ? (B + sw.rhsK - 1) / sw.rhsK : 1;
-    auto enqueue_set = [&](hipStream_t es, int b0, int nb) -> hipError_t {
+    auto enqueue_set = [&](hipStream_t es, int b0, int nb, bool start) -> hipError_t {
         TransArgs trh = tr;
         CombArgs cbh = cb;
         SweepArgs swh = sw;
@@ -1402,11 +1418,11 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
         trh.nb = cbh.nb = swh.nb = nb;
         if (fused) trh.Qc = nullptr;   // the fused kernel's first form lays ext out itself
         if (swh.rhsK > 1 && nb != B) swh.rhsK = std::max(2, std::min(DCT_MAXRC, (nb + rc_nch - 1) / rc_nch));
-        hipError_t e = launch_transition(trh, is64, es);
+        hipError_t e = start ? launch_transition(trh, is64, es) : hipSuccess;
         if (e != hipSuccess) return e;
         if (fused) {
             // first iteration of a group: q from ext in one pass over the slabs
-            if ((e = launch_dcm(cbh, ma, is64, es, 1, dcm_wg)) != hipSuccess) return e;
+            if (start && (e = launch_dcm(cbh, ma, is64, es, 1, dcm_wg)) != hipSuccess) return e;
         } else {
             if ((e = launch_mmap(ma, mode, es)) != hipSuccess) return e;
         }
@@ -1474,7 +1490,7 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
         }
         HC(hipStreamBeginCapture(ls, hipStreamCaptureModeThreadLocal));
         hipError_t ce = hipSuccess;
-        for (int c = 0; c < chunk && ce == hipSuccess; ++c) ce = enqueue_set(ls, 0, B);
+        for (int c = 0; c < chunk && ce == hipSuccess; ++c) ce = enqueue_set(ls, 0, B, true);
         hipError_t ee = hipStreamEndCapture(ls, &graph);
         HC(ce);
         HC(ee);
@@ -1509,10 +1525,10 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
         } else {
             for (int c = 0; c < chunk && sets < cap_sets; ++c, ++sets) {
                 if (hs) {
-                    HC(enqueue_set(ls, 0, hb));
-                    HC(enqueue_set(hs, hb, B - hb));
+                    HC(enqueue_set(ls, 0, hb, starts_group(sets)));
+                    HC(enqueue_set(hs, hb, B - hb, starts_group(sets)));
                 } else {
-                    HC(enqueue_set(ls, 0, B));
+                    HC(enqueue_set(ls, 0, B, starts_group(sets)));
                 }
             }
         }
