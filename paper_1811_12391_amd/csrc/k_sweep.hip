@@ -334,6 +334,8 @@ __global__ __launch_bounds__(1024) void k_sweep(SweepArgs a)
     // part of the offset a constant (rowbase).  The offsets a prefetch used
     // are kept and reused by the stores of that step PF - 1 steps later.
     int sre = __builtin_amdgcn_readfirstlane((((rstart - dr * (t0l + 1)) % nx) + nx) % nx);   // step -1
+    // (a row's length differs in a partial last tile, so it is a lane's own; the
+    // 24-bit product is one full-rate instruction: 64 x 64 x 16 FP32 56.5 -> 56.1 us)
     const unsigned lane_b = (unsigned)rowbase * TS, rwb = (unsigned)rw * TS;
     unsigned sbr[PF], ser[KEEP ? PF : 1];
     bool actr[PF];
@@ -363,8 +365,8 @@ __global__ __launch_bounds__(1024) void k_sweep(SweepArgs a)
         // idle lanes sit on their first or last row, away from the
         // active ones: an out-of-range offset keeps their loads off
         // the memory system (they return 0, never used)
-        const unsigned pp = inp ? (unsigned)(rowbase + sre * rw) : DCT_OOB;
-        const unsigned pb = inp ? lane_b + (unsigned)sre * rwb : DCT_OOB;
+        const unsigned pp = inp ? (unsigned)(rowbase + (int)__umul24(sre, rw)) : DCT_OOB;
+        const unsigned pb = inp ? lane_b + __umul24(sre, rwb) : DCT_OOB;
         sbr[ps] = pb;
         actr[ps] = inp;
         if (KEEP) ser[KEEP ? ps : 0] = pp;
@@ -698,10 +700,10 @@ __global__ __launch_bounds__(1024 / ZL) void k_sweep_lw(SweepArgs a)
 #pragma unroll
                 for (int z = 0; z < ZL; ++z) {
                     const bool inp = vz[z] && (unsigned)(tp - t0[z]) < (unsigned)nx;
-                    const unsigned pb = inp ? (unsigned)(rowbase[z] + sre[z] * rw) * TS : DCT_OOB;
+                    const unsigned pb = inp ? (unsigned)(rowbase[z] + (int)__umul24(sre[z], rw)) * TS : DCT_OOB;
                     sbr[z][ps] = pb;
                     actr[z][ps] = inp;
-                    if (KEEP) ser[KEEP ? z : 0][KEEP ? ps : 0] = inp ? (unsigned)(rowbase[z] + sre[z] * rw) : DCT_OOB;
+                    if (KEEP) ser[KEEP ? z : 0][KEEP ? ps : 0] = inp ? (unsigned)(rowbase[z] + (int)__umul24(sre[z], rw)) : DCT_OOB;
                     qr[z][ps] = bld<T>(rq, pb);
                     sr[z][ps] = bld<T>(rsg, pb);
                     sre[z] += dr;
@@ -1628,7 +1630,7 @@ __global__ __launch_bounds__(1024 / ZL) void k_sweep_rc(SweepArgs a)
                     lq[z] = st ? nq : lq[z];
                     ls[z] = st ? ns : ls[z];
                     const bool inp = vz[z] && (unsigned)(t + PF - 1 - t0[z]) < (unsigned)Knx;
-                    const unsigned cell = (unsigned)(rowbase[z] + sre[z] * rw) * TS;
+                    const unsigned cell = (unsigned)(rowbase[z] + (int)__umul24(sre[z], rw)) * TS;
                     const unsigned pb = inp ? lq[z] + cell : DCT_OOB;
                     const unsigned sb = inp ? ls[z] + cell : DCT_OOB;
                     sbr[z][ps] = pb;

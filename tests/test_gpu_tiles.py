@@ -109,3 +109,24 @@ def test_tiles_adjoint(grid, prec):
     assert a.R == b.R and np.array_equal(a.eps, b.eps)
     assert np.allclose(a.d_density, b.d_density, rtol=0, atol=1e-12 * np.abs(a.d_density).max())
     assert np.allclose(a.d_group_w, b.d_group_w, rtol=1e-12, atol=0)
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64", "fp32_bf16map"])
+@pytest.mark.parametrize("nx,ny,nz,src,sn", [(40, 64, 13, 1, 6), (33, 70, 18, 1, 4), (24, 61, 16, 9, 6)])
+def test_tuned_equals_untuned(nx, ny, nz, src, sn, prec):
+    """The tuner times schedules in both tile widths of the layouts; the solve
+    that follows, and one that takes its choice from the start, equal the
+    barrier coupling's, also with acceleration (another reader of the layouts)."""
+    prob = _problem(nx, ny, nz, src, sn)
+    fi = np.array([2, 3, 1], dtype=np.int32)
+    for kw in (dict(fixed_iters=fi), dict(tol=1e-3, max_iter=30, allow_notconv=True, accel_depth=2)):
+        st0, d0, m0 = _run(prob, precision=prec, sweep_sync=2, **kw)
+        s = dctsn.Solver(prob)
+        try:
+            for tune in (True, False):
+                st = s.solve(precision=prec, autotune=tune, **kw)
+                _say(f"[tuned] {nx}x{ny}x{nz} {prec} autotune {tune}: coupling {st.sweep_sync}")
+                assert np.array_equal(st.iters, st0.iters)
+                assert np.array_equal(s.dose(), d0) and np.array_equal(s.moments(), m0)
+        finally:
+            s.close()
