@@ -89,12 +89,20 @@ __device__ __forceinline__ Cell4<T> dd_fixup(T qv, T sv, T cx, T cy, T cz, T xin
     return c;
 }
 
-// Streaming access for the two per-direction arrays of k_sweep: q of a
-// direction is read once and psi written once per sweep, so both carry the
-// non-temporal hint (aux bit 1, NT on gfx950) and do not push the class's
-// sigma_t table, which every direction re-reads, out of the L2 (HBM bytes per
-// single-source launch 50 -> 44 MB, time unchanged).  The layered-wave kernel
-// keeps the default policy: with 36 sources the hint made it 15% slower.
+// Streaming access for the two per-direction arrays of k_sweep (the non-temporal
+// hint, aux bit 1, NT on gfx950): q of a direction is read once and psi written
+// once per sweep, so they need not push the class's sigma_t table, which every
+// direction re-reads, out of the L2 (HBM bytes per single-source launch 50 -> 44
+// MB).  The hint is right only where no line is touched by two steps.  A wave
+// step takes pieces of 16 elements: whole lines in FP64, halves in FP32, whose
+// other half the next step uses.  So q carries it in FP64 only, psi also in
+// one-block FP32 sweeps, and neither on grids whose pieces straddle the 64-byte
+// boundaries (a streamed line is fetched, or written, twice; launch_sweep).
+// Per launch, hint on all / as now: FP32 138 x 55 x 11 S8 62.5 / 55.0 us, 253 x 61
+// x 16 161 / 110, 115 x 53 x 56 with 16 sources 234 / 186, 64 x 64 x 16 with 8
+// sources 102 / 90; FP64 253 x 61 x 16 223 / 204, 115 x 53 x 56 351 / 288, 64 x
+// 64 x 16 unchanged.  The layered-wave kernel keeps the default policy: with 36
+// sources the hint made it 15% slower.
 template <typename T> __device__ inline T bld_nt(rsrc_t r, unsigned off);
 template <> __device__ inline float bld_nt<float>(rsrc_t r, unsigned off)
 {
@@ -199,8 +207,13 @@ __device__ inline bool is_empty(double v) { return __builtin_bit_cast(unsigned l
 // and passes h_out = lambda:
 //   lambda = (s + sum_{a free} c_a h_a) / (sigma + sum_{a free} c_a),
 //   h_out,a = 2 lambda - h_a (free) or lambda (fixed).
-template <typename T, int PF, bool MULTI, int SYNC, int MODE, bool PIPE>
-__global__ __launch_bounds__(1024) void k_sweep(SweepArgs a)
+//
+// NTH: non-temporal hint of psi (>= 1) and q (2).  The FP32 one-block counter
+// coupling is held to 80 VGPRs, the 6 waves a SIMD that let two workgroups of up
+// to 12 layers share a CU (88 VGPRs without the bound: 15 x 14 x 11 with 16
+// sources 82 us a launch, 57 with it).
+template <typename T, int PF, bool MULTI, int SYNC, int MODE, bool PIPE, int NTH>
+__global__ __launch_bounds__(1024, (sizeof(T) == 4 && !MULTI && SYNC && MODE != 1) ? 6 : 4) void k_sweep(SweepArgs a)
 {
     constexpr bool ADJ = MODE == 2, KEEP = MODE == 1;
     constexpr int ZR = 4;                                   // z-face ring depth (SYNC = 1)
@@ -370,7 +383,7 @@ __global__ __launch_bounds__(1024) void k_sweep(SweepArgs a)
         sbr[ps] = pb;
         actr[ps] = inp;
         if (KEEP) ser[KEEP ? ps : 0] = pp;
-        qr[ps] = bld_nt<T>(rq, pb);
+        qr[ps] = NTH == 2 ? bld_nt<T>(rq, pb) : bld<T>(rq, pb);
         sr[ps] = bld<T>(rsg, pb);
         if (ADJ) fr[ADJ ? ps : 0] = __builtin_amdgcn_raw_buffer_load_b8(rmask, pp, 0, 0);
         if (MULTI) {
@@ -553,7 +566,8 @@ __global__ __launch_bounds__(1024) void k_sweep(SweepArgs a)
                 zbuf[t & 1][ZROW ? w + 1 : w][l] = c.zo;
             }
             __builtin_amdgcn_sched_barrier(0);
-            bst_nt(rpsi, sbr[u], c.pc);
+            if (NTH > 0) bst_nt(rpsi, sbr[u], c.pc);
+            else bst(rpsi, sbr[u], c.pc);
             if (KEEP) __builtin_amdgcn_raw_buffer_store_b8((unsigned char)c.fixed, rmask, ser[KEEP ? u : 0], 0, 0);
             if (MULTI) {
                 if (PIPE) {
@@ -1862,23 +1876,31 @@ hipError_t launch_sweep(SweepArgs a, int is_f64, hipStream_t s, unsigned seq)
 #undef DCT_LW
         return hipGetLastError();
     }
-#define DCT_LAUNCH_SWEEP(T, PF, M, S, MD, P) hipLaunchKernelGGL((k_sweep<T, PF, M, S, MD, P>), grid, block, 0, s, a)
-#define DCT_LAUNCH_SWEEP_M(T, PF, M, S, P)                   \
-    do {                                                     \
-        if (mode == 2) DCT_LAUNCH_SWEEP(T, PF, M, S, 2, P);   \
-        else if (mode == 1) DCT_LAUNCH_SWEEP(T, PF, M, S, 1, P); \
-        else DCT_LAUNCH_SWEEP(T, PF, M, S, 0, P);             \
+    // streaming hints where a step's pieces of 16 rows keep to 64-byte boundaries
+    const bool nt = ((long)a.ny * (is_f64 ? 8 : 4)) % 64 == 0;
+#define DCT_LAUNCH_SWEEP(T, PF, M, S, MD, P, NT) hipLaunchKernelGGL((k_sweep<T, PF, M, S, MD, P, NT>), grid, block, 0, s, a)
+#define DCT_LAUNCH_SWEEP_M(T, PF, M, S, P, NT)                   \
+    do {                                                         \
+        if (mode == 2) DCT_LAUNCH_SWEEP(T, PF, M, S, 2, P, NT);   \
+        else if (mode == 1) DCT_LAUNCH_SWEEP(T, PF, M, S, 1, P, NT); \
+        else DCT_LAUNCH_SWEEP(T, PF, M, S, 0, P, NT);             \
     } while (0)
-#define DCT_LAUNCH_SWEEP_S(T, PF, M) \
-    do { if (a.sync) DCT_LAUNCH_SWEEP_M(T, PF, M, 1, false); else DCT_LAUNCH_SWEEP_M(T, PF, M, 0, false); } while (0)
+#define DCT_LAUNCH_SWEEP_S(T, PF, M, NT) \
+    do { if (a.sync) DCT_LAUNCH_SWEEP_M(T, PF, M, 1, false, NT); else DCT_LAUNCH_SWEEP_M(T, PF, M, 0, false, NT); } while (0)
     if (pipe) {
         // pipelined blocks keep one barrier per step inside the workgroup
-        if (is_f64) DCT_LAUNCH_SWEEP_M(double, 4, true, 0, true);
-        else DCT_LAUNCH_SWEEP_M(float, 8, true, 0, true);
+        if (is_f64 && nt) DCT_LAUNCH_SWEEP_M(double, 4, true, 0, true, 2);
+        else if (is_f64) DCT_LAUNCH_SWEEP_M(double, 4, true, 0, true, 0);
+        else DCT_LAUNCH_SWEEP_M(float, 8, true, 0, true, 0);
     } else if (is_f64) {
-        if (multi) DCT_LAUNCH_SWEEP_S(double, 4, true); else DCT_LAUNCH_SWEEP_S(double, 8, false);
+        if (multi && nt) DCT_LAUNCH_SWEEP_S(double, 4, true, 2);
+        else if (multi) DCT_LAUNCH_SWEEP_S(double, 4, true, 0);
+        else if (nt) DCT_LAUNCH_SWEEP_S(double, 8, false, 2);
+        else DCT_LAUNCH_SWEEP_S(double, 8, false, 0);
     } else {
-        if (multi) DCT_LAUNCH_SWEEP_S(float, 8, true); else DCT_LAUNCH_SWEEP_S(float, 8, false);
+        if (multi) DCT_LAUNCH_SWEEP_S(float, 8, true, 0);
+        else if (nt) DCT_LAUNCH_SWEEP_S(float, 8, false, 1);
+        else DCT_LAUNCH_SWEEP_S(float, 8, false, 0);
     }
 #undef DCT_LAUNCH_SWEEP_S
 #undef DCT_LAUNCH_SWEEP_M
