@@ -333,6 +333,7 @@ struct TransArgs {
     unsigned *cnt_sub;        // [B][nsub][32] completion sub-counters (zero between launches)
     int nsub;                 // ceil(workgroups per right-hand side / 32)
     double *part_bal;         // [B][workgroups][2] per-workgroup removal and production sums
+    int lin;                  // 1: 256 consecutive voxels a workgroup, 0: 16 x 16 of a layer
     int b0 = 0;               // the launch covers right-hand sides b0 .. b0 + nb - 1
     int nb = 0;               // (0: all B); B stays the stride of every [B] array
 };
@@ -487,6 +488,7 @@ struct AdjTransArgs {
     int *n_unfinished;
     unsigned *cnt_sub;        // [B][nsub][32] completion sub-counters (zero between launches)
     int nsub;
+    int lin;                  // as TransArgs::lin
 };
 
 struct AdjRayArgs {
@@ -533,8 +535,24 @@ hipError_t launch_sigc(const Geo &g, const uint8_t *mat, const double *rho, cons
                        void *sigc, int is_f64, hipStream_t s);
 // sigma_t of every group in the chain layout of period K nx (K copies)
 hipError_t launch_sigch(const Geo &g, const void *sigc, int G, int K, void *sigch, int is_f64, hipStream_t s);
-// workgroups of a transition: 16 x 16 voxels of a layer each
-inline long voxel_blocks(int nx, int ny, int nz) { return (long)((nx + 15) / 16) * ((ny + 15) / 16) * nz; }
+// workgroups of a transition: 256 consecutive voxels each (lin), or 16 x 16 voxels
+// of a layer
+inline long voxel_blocks(int nx, int ny, int nz, int lin)
+{
+    return lin ? ((long)nx * ny * nz + 255) / 256 : (long)((nx + 15) / 16) * ((ny + 15) / 16) * nz;
+}
+// which of the two: patches where the transition stores into the class layouts,
+// unless most of their voxels lie outside a thin grid
+inline int voxel_lin(int nx, int ny, int nz, bool stores_source)
+{
+    return !stores_source || voxel_blocks(nx, ny, nz, 0) > 2 * voxel_blocks(nx, ny, nz, 1);
+}
+// the larger of the two counts that voxel_lin chooses from
+inline long voxel_blocks_max(int nx, int ny, int nz)
+{
+    const long lin = voxel_blocks(nx, ny, nz, 1), src = voxel_blocks(nx, ny, nz, voxel_lin(nx, ny, nz, true));
+    return lin > src ? lin : src;
+}
 hipError_t launch_transition(const TransArgs &a, int is_f64, hipStream_t s);
 hipError_t launch_combine(const CombArgs &a, int is_f64, hipStream_t s);
 // Anderson acceleration: dot products and mixing coefficients, then the mixed

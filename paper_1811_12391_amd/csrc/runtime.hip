@@ -798,7 +798,7 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
     void *d_ccnt;
     HC(dbuf(ctx, "ccnt", (size_t)B * DCT_CNT_LINES * 128, &d_ccnt));
     // transition kernels: completion sub-counters and per-workgroup balance sums
-    const int tr_blocks = (int)voxel_blocks(nx, ny, nz), tr_nsub = (tr_blocks + 31) / 32;
+    const int tr_blocks = (int)voxel_blocks_max(nx, ny, nz), tr_nsub = (tr_blocks + 31) / 32;
     void *d_tsub, *d_pbal;
     HC(dbuf(ctx, "tsub", (size_t)B * tr_nsub * 128, &d_tsub));
     HC(dbuf(ctx, "pbal", (size_t)B * tr_blocks * 16, &d_pbal));
@@ -982,6 +982,7 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
     tr.cnt_sub = (unsigned *)d_tsub;
     tr.nsub = tr_nsub;
     tr.part_bal = (double *)d_pbal;
+    tr.lin = voxel_lin(nx, ny, nz, true);
     // warm start: every group starts from the moments the last solve on this
     // context left in the same buffer (same right-hand sides, groups, moments,
     // grid and precision); otherwise from phi = 0
@@ -1416,7 +1417,10 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
         SweepArgs swh = sw;
         trh.b0 = cbh.b0 = swh.b0 = b0;
         trh.nb = cbh.nb = swh.nb = nb;
-        if (fused) trh.Qc = nullptr;   // the fused kernel's first form lays ext out itself
+        if (fused) {
+            trh.Qc = nullptr;   // the fused kernel's first form lays ext out itself
+            trh.lin = voxel_lin(nx, ny, nz, false);
+        }
         if (swh.rhsK > 1 && nb != B) swh.rhsK = std::max(2, std::min(DCT_MAXRC, (nb + rc_nch - 1) / rc_nch));
         hipError_t e = start ? launch_transition(trh, is64, es) : hipSuccess;
         if (e != hipSuccess) return e;
@@ -1991,7 +1995,8 @@ static int adjoint_common(dct_ctx *ctx, const double *roi, const dct_opts *opts,
     HC(hipMemsetAsync(d_aeps, 0, (size_t)B * G * 8, s));
     HC(hipMemsetAsync(B_("err"), 0, 4, s));
     HC(hipMemsetAsync(B_("ccnt"), 0, (size_t)B * DCT_CNT_LINES * 128, s));
-    const int tr_nsub = (int)((voxel_blocks(nx, ny, nz) + 31) / 32);
+    const int lin = voxel_lin(nx, ny, nz, true);
+    const int tr_nsub = (int)((voxel_blocks(nx, ny, nz, lin) + 31) / 32);
     HC(hipMemsetAsync(B_("tsub"), 0, (size_t)B * tr_nsub * 128, s));
     HC(launch_adj_init(C, G, B, (const uint8_t *)B_("mat"), (const double *)B_("kap"), (const double *)d_roi,
                        (double *)d_pbu, s));
@@ -2041,6 +2046,7 @@ static int adjoint_common(dct_ctx *ctx, const double *roi, const dct_opts *opts,
     at.n_unfinished = (int *)B_("unf");
     at.cnt_sub = (unsigned *)B_("tsub");
     at.nsub = tr_nsub;
+    at.lin = lin;
 
     MapArgs ma;
     ma.C = C;
