@@ -129,10 +129,12 @@ typedef struct dct_opts {
                                  moment->direction map of every iteration run as one kernel
                                  per (z layer, 16 y rows) slab, with the moments and the next
                                  source kept in LDS (DCT_FP64 / DCT_FP32 only; needs the slab
-                                 tile, about 16 (L+1)^2 nx words, within the workgroup LDS);
-                                 -1: separate kernels; 0: fused when eligible and there are
-                                 at least as many slabs over all right-hand sides as the
-                                 device has compute units. */
+                                 tile, about 16 (L+1)^2 nx words, within the workgroup LDS, or
+                                 that of equal blocks of a row of at least 32 cells);
+                                 -1: separate kernels; 0: fused when eligible, there are at
+                                 least as many slabs (or blocks) over all right-hand sides as
+                                 the device has compute units, and blocks of a row in FP64 do
+                                 not cost more than the separate kernels. */
     int warm_start;           /* 1: every group starts its source iteration from the moments
                                  the previous solve on this context left (same right-hand
                                  sides, groups, P_N order, grid and precision; e.g. the next

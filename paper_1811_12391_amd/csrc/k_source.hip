@@ -17,6 +17,8 @@
 //   into phi (natural layout), measures the relative change of phi_00, builds
 //   the next within-group source Q = ext + sigma_s^{gg} phi in both class
 //   layouts, and (last block of b) applies the stopping rule.
+#include <algorithm>
+
 #include "dct_internal.h"
 
 namespace dct {
@@ -1141,16 +1143,19 @@ size_t dcm_lds_bytes(const CombArgs &a, const MapArgs &m, int is_f64, int xb)
            (size_t)2 * m.NcP * (m.NmP + 1) * ts + (size_t)4 * m.N * 4;
 }
 
-// Cells in x of a block: whole rows where they fit the LDS, else the longest of
-// 64, 48 and 32 that does (16 would double the matrix work); 0 if none does or
-// there are more blocks than completion counters.
+// Cells in x of a block: whole rows where they fit the LDS, else the fewest equal
+// blocks of 32 cells and more that do (a block takes 15 rotated rows beyond its
+// cells, so 16 would double the matrix work); 0 if none fits or there are more
+// blocks than completion counters.
 int dcm_block(const CombArgs &a, const MapArgs &m, int is_f64, size_t lds)
 {
     const int nx = a.geo.nx;
     const long per = (long)a.geo.nz * ((a.geo.ny + 15) / 16);
-    for (int xb : {nx, 64, 48, 32})
-        if (xb <= nx && dcm_lds_bytes(a, m, is_f64, xb) + 1024 <= lds)
+    for (int n = 1; n == 1 || (nx + n - 1) / n >= 32; n = std::max(n + 1, (nx + 63) / 64)) {
+        const int xb = (nx + n - 1) / n;
+        if (dcm_lds_bytes(a, m, is_f64, xb) + 1024 <= lds)
             return per * ((nx + xb - 1) / xb) <= 32L * DCT_CNT_LINES ? xb : 0;
+    }
     return 0;
 }
 
