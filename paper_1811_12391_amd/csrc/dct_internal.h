@@ -572,11 +572,12 @@ hipError_t launch_mmap(const MapArgs &a, int mode, hipStream_t s);   // mode 0 f
 hipError_t launch_dmap(const MapArgs &a, int mode, hipStream_t s);
 hipError_t launch_sweep(SweepArgs a, int is_f64, hipStream_t s, unsigned seq);
 // y streams and layer tiles per workgroup of a tile-wave sweep (SweepArgs::tS, tK),
-// S = 0 where it does not apply
+// S = 0 where it does not apply; groups: the layers of a direction may be split
+// over workgroups
 struct TilePlan {
     int S, K;
 };
-TilePlan tile_plan(int nx, int ny, int nz, long nwg, int is_f64, int ncu, size_t lds);
+TilePlan tile_plan(int nx, int ny, int nz, long nwg, int is_f64, int ncu, size_t lds, bool groups);
 hipError_t launch_dose(const DoseArgs &a, int is_f64, hipStream_t s);
 // sum_v w[v] x[v] (FP64, fixed order) into part[nb], nb = min(1024, ceil(n / 256));
 // part needs nb + 1 entries

@@ -1741,7 +1741,7 @@ __global__ __launch_bounds__(1024 / ZL) void k_sweep_rc(SweepArgs a)
 // 204 / 331, three 232 / 346, four 239 / 336; 4 streams by 2 tiles 264 / 388; 48 of
 // 256 x 256 x 64 FP32: blocks of k_sweep 1,225, 4 groups 833, 6 groups 811, 3
 // groups 984; 64 x 64 x 16 FP64: one group 79, two of 2 tiles 69, four 76).
-TilePlan tile_plan(int nx, int ny, int nz, long nwg, int is_f64, int ncu, size_t lds)
+TilePlan tile_plan(int nx, int ny, int nz, long nwg, int is_f64, int ncu, size_t lds, bool groups)
 {
     const int NKT = (nz + 3) / 4, NJ = (ny + 15) / 16;
     auto fits = [&](int S, int NK) {
@@ -1752,7 +1752,7 @@ TilePlan tile_plan(int nx, int ny, int nz, long nwg, int is_f64, int ncu, size_t
     // z groups of up to 4 tiles while every one of them gets a CU (two at least,
     // from 16 layers on): each hands its faces on some 20 us behind the one
     // below, which its waves' shorter steps have to win back
-    const long zcap = std::min<long>(std::max(2, (NKT + 3) / 4), NKT >= 4 ? ncu / std::max(1L, nwg) : 1);
+    const long zcap = std::min<long>(std::max(2, (NKT + 3) / 4), groups && NKT >= 4 ? ncu / std::max(1L, nwg) : 1);
     if (zcap > 1) {
         const int K = (NKT + (int)zcap - 1) / (int)zcap;
         for (int S = std::min(2, NJ); S > 0; --S)

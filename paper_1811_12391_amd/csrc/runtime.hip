@@ -158,6 +158,10 @@ struct dct_ctx {
     size_t lds_max = 65536;            // LDS bytes one workgroup may allocate on the device
     int ncu = 256;                     // compute units of the device
     std::string arch;                  // the device's architecture name (tune-cache key)
+    bool zg_ok = false;                // tile waves may split the layers of a direction over workgroups: their
+                                       // z faces need an L2 shared by workgroups whose indices agree mod 8, and
+                                       // no wait for a face has given up on this context
+    int test_fail_waits = 0;           // dct_test_fail_waits
     bool tface_clean = false;          // the first tface_bytes of "tface" hold only the empty marker
     size_t tface_bytes = 0;
     bool pipe_clean = false;           // pipelined-block face buffers hold only the empty marker
@@ -210,6 +214,19 @@ static bool finite_all(const double *p, size_t n)
     for (size_t i = 0; i < n; ++i)
         if (!std::isfinite(p[i])) return false;
     return true;
+}
+
+// whether a bounded wait of the iterations just finished gave up
+static hipError_t wait_gave_up(dct_ctx *ctx, const void *d_err, bool *gave_up)
+{
+    int h = 0;
+    const hipError_t e = hipMemcpy(&h, d_err, 4, hipMemcpyDeviceToHost);
+    *gave_up = h != 0;
+    if (ctx->test_fail_waits > 0) {
+        --ctx->test_fail_waits;
+        *gave_up = true;
+    }
+    return e;
 }
 
 static void tune_cache_load(dct_ctx *ctx)
@@ -294,6 +311,9 @@ int dct_create(dct_ctx **out, int device, void *stream)
             int ncu = 0;
             if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, device) == hipSuccess && ncu > 0)
                 ctx->ncu = ncu;
+            int xcc = 0;
+            ctx->zg_ok = hipDeviceGetAttribute(&xcc, hipDeviceAttributeNumberOfXccs, device) == hipSuccess && xcc > 0 &&
+                         8 % xcc == 0;
             hipDeviceProp_t prop;
             if (hipGetDeviceProperties(&prop, device) == hipSuccess) {
                 ctx->arch = prop.gcnArchName;
@@ -340,6 +360,16 @@ int dct_destroy(dct_ctx *ctx)
         if (ctx->h_stage) (void)hipHostFree(ctx->h_stage);
     }
     delete ctx;
+    return DCT_OK;
+}
+
+// For the library's tests, not part of the interface: the next n iteration loops
+// (of solves and adjoints) count as if one of their bounded waits had given up,
+// without anything being provoked on the device.
+int dct_test_fail_waits(dct_ctx *ctx, int n)
+{
+    if (!ctx || n < 0) return DCT_EINVAL;
+    ctx->test_fail_waits = n;
     return DCT_OK;
 }
 
@@ -779,7 +809,7 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
         if (d_hint != old_h) HC(hipMemsetAsync(d_hint, 0, (size_t)B * N * pl.NBJ * ((nz + 1) / 2) * 8, s));
     }
     // z faces between the groups of a tile-wave sweep, empty between launches
-    const TilePlan tile = tile_plan(nx, ny, nz, (long)B * N, is64, ctx->ncu, ctx->lds_max);
+    const TilePlan tile = tile_plan(nx, ny, nz, (long)B * N, is64, ctx->ncu, ctx->lds_max, ctx->zg_ok);
     const int tile_zg = tile.S > 0 ? ((nz + 3) / 4 + tile.K - 1) / tile.K : 1;
     void *d_tf = nullptr;
     if (tile_zg > 1) {
@@ -990,6 +1020,7 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
                       ctx->warm.Nm == Nm && ctx->warm.C == C && ctx->warm.prec == o.precision &&
                       ctx->warm.phi == d_phi;
     tr.warm = warm ? 1 : 0;
+    ctx->warm.valid = false;   // the moments are overwritten from here on, whatever becomes of this solve
     // Anderson acceleration of the within-group iteration (depth accel_depth)
     const int aam = o.accel_depth;
     AAArgs aa;
@@ -1304,6 +1335,7 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
                         // flag and the handed-over faces
                         HC(hipMemsetAsync(d_err, 0, 4, s));
                         ctx->pipe_clean = ctx->tface_clean = false;
+                        if (sw.tS > 0 && tile_zg > 1) ctx->zg_ok = false;
                         continue;
                     }
                     float ms = 0.0f;
@@ -1601,11 +1633,19 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
     HC(hipMemcpy(fin.data(), d_state, (size_t)B * sizeof(RhsState), hipMemcpyDeviceToHost));
     std::vector<int> iters((size_t)B * G);
     HC(hipMemcpy(iters.data(), d_iters, iters.size() * 4, hipMemcpyDeviceToHost));
-    int h_err = 0;
-    HC(hipMemcpy(&h_err, d_err, 4, hipMemcpyDeviceToHost));
-    if (h_err) {
+    bool gave_up = false;
+    HC(wait_gave_up(ctx, d_err, &gave_up));
+    if (gave_up) {
         ctx->solved = false;
         ctx->pipe_clean = ctx->tface_clean = false;
+        if (sw.tS > 0 && tile_zg > 1 && ctx->zg_ok) {
+            // nobody asked for waits between workgroups: this context stops using
+            // them and solves again.  (A warm start's moments are spoiled: the solve
+            // starts from zero, which a prescribed count would not make up for.)
+            ctx->zg_ok = false;
+            dlog(1, "a wait for a z face gave up: layers of a direction stay in one workgroup from now on");
+            if (!(warm && o.fixed_iters)) return dct_solve(ctx, opts, stats);
+        }
         return fail(ctx, DCT_EDEVICE, "solve: a sweep wave wait exceeded its bound (inter-wave synchronisation)");
     }
     int status = DCT_OK;
@@ -2125,7 +2165,7 @@ static int adjoint_common(dct_ctx *ctx, const double *roi, const dct_opts *opts,
     sw.layers = 0;
     // transposed sweeps: tile waves after a tile-wave forward solve, otherwise
     // k_sweep (barrier coupling for layered schedules)
-    const TilePlan tile = tile_plan(nx, ny, nz, (long)B * N, is64, ctx->ncu, ctx->lds_max);
+    const TilePlan tile = tile_plan(nx, ny, nz, (long)B * N, is64, ctx->ncu, ctx->lds_max, ctx->zg_ok);
     sw.tS = ctx->last_sync == 4 ? tile.S : 0;
     if (sw.tS > 0) {
         sw.tK = tile.K;
@@ -2138,6 +2178,15 @@ static int adjoint_common(dct_ctx *ctx, const double *roi, const dct_opts *opts,
     sw.sigch = nullptr;
     sw.yface_p = B_("yfp");
     sw.zface_p = B_("zfp");
+    // faces handed over inside a launch start out empty, also after a call that gave up
+    if (sw.pipe && !ctx->pipe_clean) {
+        for (const char *n : {"yfp", "zfp"}) HC(hipMemsetAsync(B_(n), 0xff, ctx->bufs[n].bytes, s));
+        ctx->pipe_clean = true;
+    }
+    if (sw.tS > 0 && sw.nblk > 1 && !ctx->tface_clean) {
+        HC(hipMemsetAsync(sw.tface, 0xff, ctx->tface_bytes, s));
+        ctx->tface_clean = true;
+    }
     sw.hint = (unsigned long long *)B_("hint");
     sw.seq = 0;
     sw.err = (int *)B_("err");
@@ -2218,10 +2267,16 @@ static int adjoint_common(dct_ctx *ctx, const double *roi, const dct_opts *opts,
     HC(launch_adj_ray(ar, s));
     HC(hipEventRecord(ctx->ev_t1, s));
     HC(hipEventSynchronize(ctx->ev_t1));
-    int h_err = 0;
-    HC(hipMemcpy(&h_err, B_("err"), 4, hipMemcpyDeviceToHost));
-    if (h_err) {
+    bool gave_up = false;
+    HC(wait_gave_up(ctx, B_("err"), &gave_up));
+    if (gave_up) {
         ctx->pipe_clean = ctx->tface_clean = false;
+        if (sw.tS > 0 && sw.nblk > 1 && ctx->zg_ok) {
+            // as in dct_solve; what the forward solve kept is untouched
+            ctx->zg_ok = false;
+            dlog(1, "a wait for a z face gave up: layers of a direction stay in one workgroup from now on");
+            return adjoint_common(ctx, roi, opts, R, d_density, d_group_w, stats, dev);
+        }
         return fail(ctx, DCT_EDEVICE, "adjoint: a sweep wave wait exceeded its bound");
     }
     if (unfinished != 0) return fail(ctx, DCT_ENOTCONV, "adjoint: iteration-set cap reached");
