@@ -902,6 +902,7 @@ __global__ __launch_bounds__(1024) void k_sweep_t(SweepArgs a)
     constexpr int BG = DCT_TILE_BG, RS = 2 * BG;             // z ring slots
     constexpr int U = PF > RS ? PF : RS;                     // unrolled steps
     constexpr int LZ = 7 + BG;
+    constexpr int ZS = 2;                                    // y streams at most with z groups (tile_plan)
     static_assert(U % PF == 0 && U % RS == 0 && BG == 4, "ring slots are constants of the unrolled loop");
     static_assert(PF + BG + DCT_TILE_SKEW <= DCT_TILE_XMIN, "the next tile is set up before a lane starts it");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_t[];
@@ -1073,10 +1074,10 @@ __global__ __launch_bounds__(1024) void k_sweep_t(SweepArgs a)
                 bst_dev(rout, where(q, tau, q * DCT_TILE_LY + (NK - 1) * LZ + 6), v);
             }
         };
-        T v[4] = {(T)0, (T)0, (T)0, (T)0};
+        T v[ZS] = {(T)0, (T)0};
         if (cons)
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
+            for (int q = 0; q < ZS; ++q)
                 if (q < S) v[q] = bld_dev<T>(rin, where(q, -U + kl + BG + 1, q * DCT_TILE_LY));
         for (int tb = -U; tb < NT; tb += U)
 #pragma unroll 1
@@ -1086,7 +1087,7 @@ __global__ __launch_bounds__(1024) void k_sweep_t(SweepArgs a)
                 if (cons) {
                     // step tau = t + kl of the wave below: used at tau + BG + 1
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
+                    for (int q = 0; q < ZS; ++q) {
                         if (q >= S) break;
                         const unsigned o = where(q, t + kl + BG + 1, q * DCT_TILE_LY);
                         while (__builtin_amdgcn_ballot_w64(is_empty(v[q])) != 0 && spins < DCT_SPIN_LIMIT) {
@@ -1826,7 +1827,7 @@ hipError_t launch_sweep(SweepArgs a, int is_f64, hipStream_t s, unsigned seq)
         const int NKT = (a.nz + 3) / 4, NK = a.tK > 0 ? a.tK : NKT, NJ = (a.ny + 15) / 16;
         const int nzg = (NKT + NK - 1) / NK;
         const bool zgr = nzg > 1;
-        if (a.tS > NJ || a.tS * NK + (zgr ? 1 : 0) > 16 || (zgr && (a.tS > 4 || !a.tface)) || a.pipe || a.inflow ||
+        if (a.tS > NJ || a.tS * NK + (zgr ? 1 : 0) > 16 || (zgr && (a.tS > 2 || !a.tface)) || a.pipe || a.inflow ||
             a.nblk != nzg)
             return hipErrorInvalidValue;
         const dim3 tgrid(zgr ? 8u * (unsigned)(((long)a.N * nb + 7) / 8) : (unsigned)a.N, zgr ? 1u : (unsigned)nb,
