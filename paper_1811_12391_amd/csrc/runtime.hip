@@ -71,8 +71,11 @@ __attribute__((format(printf, 2, 3))) void dlog(int level, const char *fmt, ...)
 // Persisted sweep schedules: with DCT_TUNE_CACHE = path, every tuning result
 // is appended to that text file as one line, and a new context on a device of
 // the same architecture and compute-unit count starts from the file's entries
-// (the last entry of a shape wins), so a new process need not tune again.
+// (the last entry of a shape wins), so a new process need not tune again.  A line
+// ends with the version of the schedules it was timed on and the form of the
+// tuning; lines of another version (the first had neither) are not used.
 constexpr const char *kTuneTag = "dctsn-tune-1";
+constexpr int kTuneVersion = 2;   // 2: layouts of 16 rows, coupling 4 = tile waves
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
@@ -140,6 +143,7 @@ struct dct_ctx {
     // sweep schedules chosen by the autotuner, per problem shape
     struct Tuned {
         int nx, ny, nz, N, B, prec, keep, bk, sync, chain, rhs;
+        int form;   // what the candidates were: the schedule options given, an inflow, tile waves' z groups
     };
     std::vector<Tuned> tuned;
     int last_bk = 16, last_sync = 1;   // schedule of the last solve (reused by the adjoint)
@@ -239,11 +243,12 @@ static void tune_cache_load(dct_ctx *ctx)
     int n = 0;
     while (std::fgets(line, sizeof(line), f)) {
         dct_ctx::Tuned t;
-        int ncu = 0;
-        if (std::sscanf(line, "%31s %127s %d %d %d %d %d %d %d %d %d %d %d %d", tag, arch, &ncu, &t.nx, &t.ny, &t.nz,
-                        &t.N, &t.B, &t.prec, &t.keep, &t.bk, &t.sync, &t.chain, &t.rhs) != 14)
+        int ncu = 0, version = 0;
+        if (std::sscanf(line, "%31s %127s %d %d %d %d %d %d %d %d %d %d %d %d %d %d", tag, arch, &ncu, &t.nx, &t.ny,
+                        &t.nz, &t.N, &t.B, &t.prec, &t.keep, &t.bk, &t.sync, &t.chain, &t.rhs, &version,
+                        &t.form) != 16)
             continue;
-        if (std::strcmp(tag, kTuneTag) != 0 || ctx->arch != arch || ncu != ctx->ncu) continue;
+        if (std::strcmp(tag, kTuneTag) != 0 || version != kTuneVersion || ctx->arch != arch || ncu != ctx->ncu) continue;
         ctx->tuned.push_back(t);
         ++n;
     }
@@ -256,9 +261,9 @@ static void tune_cache_save(const dct_ctx *ctx, const dct_ctx::Tuned &t)
     const char *path = std::getenv("DCT_TUNE_CACHE");
     if (!path || !*path) return;
     char line[512];
-    const int len = std::snprintf(line, sizeof(line), "%s %s %d %d %d %d %d %d %d %d %d %d %d %d\n", kTuneTag,
+    const int len = std::snprintf(line, sizeof(line), "%s %s %d %d %d %d %d %d %d %d %d %d %d %d %d %d\n", kTuneTag,
                                   ctx->arch.c_str(), ctx->ncu, t.nx, t.ny, t.nz, t.N, t.B, t.prec, t.keep, t.bk,
-                                  t.sync, t.chain, t.rhs);
+                                  t.sync, t.chain, t.rhs, kTuneVersion, t.form);
     FILE *f = std::fopen(path, "a");
     if (!f) {
         dlog(1, "tune cache %s: cannot append", path);
@@ -1255,10 +1260,15 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
         // the maps some address arithmetic
         const bool free_bk = o.sweep_bk == 0, free_cpl = o.sweep_sync == 0, free_chain = o.sweep_chain < 0;
         if (o.autotune && (free_bk || free_cpl || free_chain)) {
+            // a choice holds for the candidates it was made among
+            const int ask_chain = o.sweep_chain < 0 ? DCT_MAXCHAIN + 1 : (o.sweep_chain > 1 ? o.sweep_chain : 0);
+            int form = (o.sweep_bk * 11 + o.sweep_sync) * (DCT_MAXCHAIN + 2) + ask_chain;
+            form = (form * (DCT_MAXRC + 1) + o.sweep_rhs_chain) * 2 + (o.test_inflow ? 1 : 0);
+            form = form * 64 + (tile_ok ? std::min(tile_zg, 63) : 0);
             const dct_ctx::Tuned *hit = nullptr;
             for (const auto &t : ctx->tuned)
                 if (t.nx == nx && t.ny == ny && t.nz == nz && t.N == N && t.B == B && t.prec == o.precision &&
-                    t.keep == (int)keep)
+                    t.keep == (int)keep && t.form == form)
                     hit = &t;
             if (hit) {
                 if (free_bk) bk = hit->bk;
@@ -1352,7 +1362,7 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
                     }
                 }
                 if (best == 1e30f) return fail(ctx, DCT_EDEVICE, "solve: no sweep schedule completed during tuning");
-                ctx->tuned.push_back({nx, ny, nz, N, B, o.precision, (int)keep, bk, cpl, chainK, rhsK});
+                ctx->tuned.push_back({nx, ny, nz, N, B, o.precision, (int)keep, bk, cpl, chainK, rhsK, form});
                 tune_cache_save(ctx, ctx->tuned.back());
                 dlog(1, "tuned %dx%dx%d N=%d B=%d precision %d: z layers %d, coupling %d, chained directions %d, "
                         "chained sources %d (%.2f ms per sweep)", nx, ny, nz, N, B, o.precision, bk, cpl, chainK, rhsK,
