@@ -1298,10 +1298,12 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
                 } else {
                     bks.push_back(std::min(bk, nz));
                 }
+                // tile waves asked for where they do not apply run as the barrier coupling
+                const int asked = cpl == 4 && layered_ok && !tile_ok ? 2 : cpl;
                 for (int cb : bks) {
                     const bool multi = (ny + 63) / 64 > 1 || (nz + cb - 1) / cb > 1;
                     for (int cc : {1, 2, 3, 4, 5, 6, 7, 8, 9, 10}) {
-                        if (!free_cpl && cc != cpl) continue;
+                        if (!free_cpl && cc != asked) continue;
                         if (cc == 3 && (!multi || cb < 2)) continue;   // pipelining needs several blocks
                         // one block of every layer
                         if (cc >= 4 && cb != std::min(16, nz)) continue;

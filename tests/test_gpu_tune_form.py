@@ -74,3 +74,18 @@ def test_cache_lines_of_other_schedules(tmp_path, monkeypatch):
         assert s.solve(**dict(kw, test_inflow=INFLOW)).tune_ms > 0
     finally:
         s.close()
+
+
+def test_forced_tile_waves_with_inflow():
+    """Coupling 4 asked for with an inflow runs as the barrier coupling, tuned as
+    untuned."""
+    prob = _problem(21, 35, 7)
+    kw = dict(precision="fp64", fixed_iters=np.array([2, 2], dtype=np.int32), sweep_sync=4, test_inflow=INFLOW)
+    s = dctsn.Solver(prob)
+    try:
+        a = s.solve(**kw)
+        d = s.dose()
+        b = s.solve(autotune=True, **kw)
+        assert (a.sweep_sync, b.sweep_sync) == (2, 2) and np.array_equal(s.dose(), d)
+    finally:
+        s.close()
