@@ -1235,8 +1235,8 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
     auto pipe_ready = [&]() -> int {
         // faces handed over inside a launch start out empty (all bits set)
         if (!ctx->pipe_clean) {
-            HC(hipMemsetAsync(d_yfp, 0xff, yfp_bytes, s));
-            HC(hipMemsetAsync(d_zfp, 0xff, zfp_bytes, s));
+            // the whole buffers: a later solve of a larger shape may use more of them
+            for (const char *n : {"yfp", "zfp"}) HC(hipMemsetAsync(ctx->bufs[n].p, 0xff, ctx->bufs[n].bytes, s));
             ctx->pipe_clean = true;
         }
         return DCT_OK;

@@ -146,3 +146,28 @@ def test_failed_solve_leaves_no_warm_start():
         assert e.value.code == dctsn.DCT_EDEVICE
     finally:
         s.close()
+
+
+def test_pipelined_blocks_on_a_buffer_of_another_shape():
+    """The hand-over buffers are as large as the largest solve so far: a small
+    pipelined solve and then a large one find them empty throughout."""
+    big, small = _problem(40, 130, 20), _problem(12, 70, 4)
+    kw = dict(precision="fp64", fixed_iters=FI, sweep_bk=4, sweep_sync=3)
+    def load(s, prob):
+        ph, xs = prob.phantom, prob.xs
+        dctsn.set_geometry(s.h, ph.nx, ph.ny, ph.nz, ph.dx, ph.dy, ph.dz, ph.origin, ph.material, ph.density)
+        dctsn.set_xs(s.h, xs.G, xs.edges, xs.M, prob.L, xs.sigma_t, xs.sigma_s[:, : prob.L + 1], xs.kerma)
+        dctsn.set_source(s.h, prob.B, prob.src_pos, prob.src_axis, prob.fan_deg, prob.cone_deg, prob.group_w)
+        s.prob = prob
+
+    s = dctsn.Solver(big)
+    try:
+        s.solve(precision="fp64", fixed_iters=FI, sweep_bk=16, sweep_sync=2)
+        d = s.dose()
+        load(s, small)
+        assert s.solve(**dict(kw, sweep_bk=2)).sweep_sync == 3
+        load(s, big)
+        assert s.solve(**kw).sweep_sync == 3
+        assert np.array_equal(s.dose(), d)
+    finally:
+        s.close()
