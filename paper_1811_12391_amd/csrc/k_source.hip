@@ -338,7 +338,8 @@ __global__ __launch_bounds__(256) void k_adj_transition(AdjTransArgs a)
             // is read and written once, not once a moment (each sum keeps its
             // order: scattered flux of g2 < gp, then the uncollided terms).  With
             // the 16 x 16 voxel blocks and the source laid out here, a gradient
-            // at 64 x 64 x 16, S8 P3, 19 groups went from 35.3 to 32.7 ms.
+            // at 64 x 64 x 16, S6 P3, 19 groups went from 35.3 to 32.7 ms on the class
+            // layouts of that time, whole rows of y (on those of 16 rows: 33.1).
             const T *lamg = lam_all + ((long)b * G + gp) * Nm * C;
             const double *sm = a.ss + (long)m * (L + 1) * G * G;
             double lv[NM], dq[NM];

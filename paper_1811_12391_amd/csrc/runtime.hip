@@ -147,6 +147,7 @@ struct dct_ctx {
     };
     std::vector<Tuned> tuned;
     int last_bk = 16, last_sync = 1;   // schedule of the last solve (reused by the adjoint)
+    bool last_asked = false;           // its coupling was asked for by number
     int last_chain = 1;
     int last_rhs = 1;
     bool last_fused = false;
@@ -593,6 +594,27 @@ static void set_blocks(Plan &pl, int bk, int ny, int nz)
     pl.NBK = (nz + pl.BK - 1) / pl.BK;
     pl.nblk = pl.NBJ * pl.NBK;
     pl.ndiag = pl.NBJ + pl.NBK - 1;
+}
+
+// Where the barrier coupling is taken before tile waves untuned, and by the
+// transposed sweeps that follow tile waves.  nwg: directions of all sources.
+//
+// One block (a direction is one workgroup of nz waves): while every wave of the
+// barrier coupling has a slot at four a SIMD its fewer steps win, up to 12 layers;
+// from 13 on tile waves split the layers over compute units, which wins in FP64,
+// and in FP32 once there are more directions than those.  Several blocks: only
+// on grids so short in x and z that a tile's skew is most of its steps.  Timed on
+// 449 random sizes (us an iteration, separate maps, barrier / tiles): FP64 44 x 50 x
+// 11 with 96 directions 86 / 100, 120 x 36 x 12 with 144 143 / 146, 52 x 21 x 13
+// with 48 76 / 75, 83 x 20 x 16 with 80 102 / 91; 384 and 960 directions: 19 x 9 x 4
+// 38 / 43, 37 x 12 x 12 0.58 of the barrier's; FP32 94 x 48 x 14 with 48 100 / 110,
+// 19 x 10 x 14 with 384 0.88 of it; 5 x 119 x 5 with 80 81 / 100, 40 x 97 x 10 with
+// 80 124 / 102.  The rule's choice is 1% behind the better of the three couplings
+// in the mean (tiles wherever nz > 8 or FP32 directions exceed the units: 5.6%).
+static bool barrier_first(int nx, int ny, int nz, long nwg, bool is64, int ncu)
+{
+    if (ny <= 64 && nz <= 16) return nwg * nz <= 16L * ncu && (nz <= 12 || (!is64 && nwg <= ncu));
+    return nz <= 8 && nx * nz <= 96;
 }
 
 static int check_consistency(dct_ctx *ctx, const dct_opts &o, Plan &pl)
@@ -1244,13 +1266,8 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
     int chainK = 1, rhsK = 1;
     {
         int bk = o.sweep_bk > 0 ? o.sweep_bk : 16;
-        // untuned: tile waves, except that with a CU to itself for every
-        // direction of a one-block grid the barrier coupling's fewer steps are
-        // faster in FP32 and on up to 8 layers (us an iteration, barrier / tiles:
-        // 24 x 24 x 8 FP64 42.1 / 45.6, 64 x 64 x 16 FP32 93.6 / 97.1, but 61 x 45 x
-        // 13 FP64 120 / 115, 64 x 64 x 16 FP64 136 / 116)
         int cpl = o.sweep_sync > 0 ? o.sweep_sync
-                                   : (!free_sched || !tile_ok ? 1 : (layered_ok && (long)B * N <= ctx->ncu && (!is64 || nz <= 8) ? 2 : 4));
+                                   : (!free_sched || !tile_ok ? 1 : (barrier_first(nx, ny, nz, (long)B * N, is64, ctx->ncu) ? 2 : 4));
         chainK = o.sweep_chain > 1 ? o.sweep_chain :
                  ((cpl >= 6 && cpl <= 8 && !chain_ks.empty()) ? chain_ks.back() : 1);
         rhsK = o.sweep_rhs_chain > 0 ? o.sweep_rhs_chain : std::min(B, 4);
@@ -1394,6 +1411,7 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
         }
         ctx->last_bk = pl.BK;
         ctx->last_sync = cpl;
+        ctx->last_asked = o.sweep_sync > 0;
         ctx->last_chain = chainK;
         ctx->last_rhs = rhsK;
     }
@@ -2175,10 +2193,14 @@ static int adjoint_common(dct_ctx *ctx, const double *roi, const dct_opts *opts,
     sw.sync = ctx->last_sync == 1;
     sw.pipe = ctx->last_sync == 3;
     sw.layers = 0;
-    // transposed sweeps: tile waves after a tile-wave forward solve, otherwise
-    // k_sweep (barrier coupling for layered schedules)
+    // transposed sweeps: tile waves after a tile-wave forward solve, unless it took
+    // them untuned or tuned where the barrier coupling sweeps the transposed cells
+    // faster (the tuner times forward sweeps: 64 x 64 x 16 S6 FP32, adjoint 16.1 ms
+    // on tile waves, 15.6 so); otherwise k_sweep (barrier coupling for layered
+    // schedules)
     const TilePlan tile = tile_plan(nx, ny, nz, (long)B * N, is64, ctx->ncu, ctx->lds_max, ctx->zg_ok);
-    sw.tS = ctx->last_sync == 4 ? tile.S : 0;
+    const bool barrier = !ctx->last_asked && barrier_first(nx, ny, nz, (long)B * N, is64, ctx->ncu);
+    sw.tS = ctx->last_sync == 4 && !barrier ? tile.S : 0;
     if (sw.tS > 0) {
         sw.tK = tile.K;
         sw.tface = B_("tface");
