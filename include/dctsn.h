@@ -87,8 +87,9 @@ typedef struct dct_opts {
                                  as they are produced (needs >= 2 blocks of >= 2 z layers,
                                  otherwise runs as 1), 4 = tile waves: every wave sweeps tiles
                                  of 4 z layers x 16 y rows, one barrier per 4 steps (needs
-                                 ny <= 64, nz <= 16, sweep_bk >= nz, no test_inflow; otherwise
-                                 runs as 2), 5 = layered waves: every wave
+                                 ny <= 64, nz <= 16, sweep_bk >= nz (or as dct_stats reports
+                                 it), no test_inflow, and the faces within the workgroup LDS;
+                                 otherwise runs as 2), 5 = layered waves: every wave
                                  sweeps 2 z layers as a skewed pipeline in registers,
                                  one barrier per step (needs one block: ny <= 64, nz <= 16,
                                  sweep_bk >= nz; otherwise runs as 2; the transposed sweeps
@@ -96,8 +97,13 @@ typedef struct dct_opts {
                                  (sweep_chain) with 1 / 2 / 4 z layers per wave; 9 / 10 =
                                  chained right-hand sides (sweep_rhs_chain) with 2 / 1 z
                                  layers per wave; 0 = tuned, or (with sweep_bk and sweep_chain
-                                 free too) tile waves on any grid of up to 64 layers, coupling
-                                 2 for few directions on a grid of one block, else 1 */
+                                 free too) tile waves where their faces fit the LDS (up to 64
+                                 layers, more for few directions), with the layers of a
+                                 direction over several workgroups when there are compute
+                                 units to spare; coupling 2 on small one-block grids and very
+                                 short ones; else 1.  A wait between the workgroups of the
+                                 untuned or tuned choice that gives up is not an error: the
+                                 call runs again without such waits */
     int superpose;            /* sources per right-hand side S (0 or 1: one each).  With
                                  S > 1 the B sources of dct_set_source form B / S right-hand
                                  sides of S consecutive sources; each is solved once with
@@ -184,7 +190,8 @@ typedef struct dct_stats {
     double sweep_ms;          /* summed device time of the timed sweep launches (profile > 0) */
     double solve_ms;          /* device time of the whole dct_solve (HIP events) */
     int iteration_sets;       /* iteration launch sets enqueued (>= max over RHS of iterations) */
-    int sweep_bk;             /* sweep schedule that ran: z layers per workgroup */
+    int sweep_bk;             /* sweep schedule that ran: z layers per workgroup (of a z group
+                                 with coupling 4) */
     int sweep_sync;           /* and coupling (1 LDS counters, 2 barriers, 3 pipelined blocks,
                                  4 tile waves, 5 layered waves of 2 z layers, 6 / 7 / 8 chained
                                  directions with 1 / 2 / 4 z layers per wave, 9 / 10 chained

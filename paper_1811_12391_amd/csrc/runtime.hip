@@ -1223,6 +1223,7 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
     // LDS when the schedule is free, the layered waves' grids when asked for
     const bool free_sched = o.sweep_bk == 0 && o.sweep_sync == 0 && o.sweep_chain <= 1;
     const bool tile_ok = tile.S > 0 && (free_sched || layered_ok) && !o.test_inflow;
+    const int tile_layers = std::min(4 * tile.K, nz);   // z layers of a tile-wave workgroup
     auto set_coupling = [&](int cpl) {
         sw.tS = cpl == 4 && tile_ok ? tile.S : 0;
         if (sw.tS > 0) {
@@ -1390,7 +1391,8 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
         }
         apply_blocks(bk);
         if (cpl == 3 && (pl.nblk == 1 || pl.BK < 2)) cpl = 1;   // one block (or 1-layer blocks): not pipelined
-        if (cpl == 4 && (!tile_ok || (!free_sched && pl.nblk != 1))) cpl = 2;
+        // (a block height as the statistics report it is one of tile waves too)
+        if (cpl == 4 && (!tile_ok || (!free_sched && pl.nblk != 1 && o.sweep_bk != tile_layers))) cpl = 2;
         if (cpl == 5 && (!layered_ok || pl.nblk != 1)) cpl = 2;   // layered waves need one block
         if (cpl >= 6 && cpl <= 8 &&
             (pl.nblk != 1 || std::find(chain_ks.begin(), chain_ks.end(), chainK) == chain_ks.end())) {
@@ -1712,7 +1714,7 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
         stats->fused_launches = nprof_m;
         stats->sweep_launches_all = (long long)sets * (sw.pipe ? 1 : pl.ndiag) * nstreams;
         stats->iteration_sets = (int)sets;
-        stats->sweep_bk = pl.BK;
+        stats->sweep_bk = sw.tS > 0 ? tile_layers : pl.BK;
         stats->sweep_sync = ctx->last_sync;
         stats->sweep_chain = ctx->last_chain;
         stats->sweep_rhs_chain = ctx->last_rhs;
