@@ -1145,19 +1145,23 @@ size_t dcm_lds_bytes(const CombArgs &a, const MapArgs &m, int is_f64, int xb)
 }
 
 // Cells in x of a block: whole rows where they fit the LDS, else the fewest equal
-// blocks of 32 cells and more that do (a block takes 15 rotated rows beyond its
-// cells, so 16 would double the matrix work); 0 if none fits or there are more
-// blocks than completion counters.
+// blocks of 32 to 64 cells that do (a block takes 15 rotated rows beyond its cells,
+// so 16 would double the matrix work), else blocks of 32 and a rest; 0 if none fits
+// or there are more blocks than completion counters.
 int dcm_block(const CombArgs &a, const MapArgs &m, int is_f64, size_t lds)
 {
     const int nx = a.geo.nx;
     const long per = (long)a.geo.nz * ((a.geo.ny + 15) / 16);
-    for (int n = 1; n == 1 || (nx + n - 1) / n >= 32; n = std::max(n + 1, (nx + 63) / 64)) {
-        const int xb = (nx + n - 1) / n;
-        if (dcm_lds_bytes(a, m, is_f64, xb) + 1024 <= lds)
-            return per * ((nx + xb - 1) / xb) <= 32L * DCT_CNT_LINES ? xb : 0;
+    auto fits = [&](int xb) { return dcm_lds_bytes(a, m, is_f64, xb) + 1024 <= lds; };
+    int xb = nx;
+    for (int n = (nx + 63) / 64; !fits(xb); ++n) {
+        xb = (nx + n - 1) / n;
+        if (xb < 32) {
+            xb = 32;
+            if (nx < 32 || !fits(xb)) return 0;
+        }
     }
-    return 0;
+    return per * ((nx + xb - 1) / xb) <= 32L * DCT_CNT_LINES ? xb : 0;
 }
 
 hipError_t launch_dcm(const CombArgs &a, const MapArgs &m, int is_f64, hipStream_t s, int first, int max_wg)

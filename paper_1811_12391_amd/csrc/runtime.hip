@@ -1432,18 +1432,18 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
     const long nblocks = (long)nz * nyb * nxb * B;
     // persistent workgroups: as many as fit the device at once
     const int dcm_wg = (fuse_ok && 2 * (dcm_lds_bytes(cb, ma, is64, cb.xb) + 1024) <= ctx->lds_max ? 2 : 1) * ctx->ncu;
-    // blocks of a row in FP64 have to win back the rows they take beyond their
-    // cells and the blocks' last round: the separate kernels move (2 N + 10 Nm) / (2 N
-    // + 2 Nm) times the bytes.  Both timed on 180 random sizes, an iteration of the
-    // separate kernels / fused: 0.96 - 1.09 below the line, mostly under 1 (S8 P1 282 x 16 x 7 0.96, S8 P4
-    // 64 x 80 x 27 0.98, S6 P3 94 x 18 x 25 with 8 sources 1.09), above it 0.99 - 1.44
-    // (S8 P3 128 x 144 x 30 1.05, S6 P3 256 x 64 x 21 with 8 sources 1.44); FP32 1.05 -
-    // 1.55 throughout
+    // blocks of a row have to win back the rows they take beyond their cells and
+    // the blocks' last round: the separate kernels move (2 N + 10 Nm) / (2 N + 2 Nm)
+    // times the bytes.  Timed on 240 random sizes, an iteration of the separate kernels
+    // / fused: FP64 0.96 - 1.09 below the line, mostly under 1 (S8 P1 282 x 16 x 7
+    // 0.96, S8 P4 64 x 80 x 27 0.98, S6 P3 94 x 18 x 25 with 8 sources 1.09), above it
+    // 0.99 - 1.44 (S8 P3 128 x 144 x 30 1.05, S6 P3 256 x 64 x 21 with 8 sources 1.44);
+    // FP32 1.05 - 1.55 above its line, and S8 P4 88 x 1 x 8 with 16 sources 0.81 below
     bool pays = nblocks >= ctx->ncu;
-    if (pays && is64 && nxb > 1) {
+    if (pays && nxb > 1) {
         const double rows = (nx + 15.0 * nxb) / nx * 16.0 * nyb / ny;
         const double rounds = (double)((nblocks + dcm_wg - 1) / dcm_wg) * dcm_wg / nblocks;
-        pays = (N + 5.0 * Nm) / (N + Nm) >= 0.71 * rows * rounds;
+        pays = (N + 5.0 * Nm) / (N + Nm) >= (is64 ? 0.71 : 0.5) * rows * rounds;
     }
     const bool fused = fuse_ok && aam == 0 && (o.fuse_maps > 0 || (o.fuse_maps == 0 && pays));
     ma.first_only = fused ? 1 : 0;

@@ -2,7 +2,7 @@
 blocks narrower than 64 cells and on rows barely longer than a block, so that the
 class rotation wraps within it: moments and dose equal the separate map kernels'
 bit for bit.  Block widths as the library chooses them: the fewest equal blocks
-of at most 64 and at least 32 cells that fit the workgroup's LDS."""
+of at most 64 and at least 32 cells that fit the workgroup's LDS, else 32 and a rest."""
 import numpy as np
 import pytest
 
@@ -45,16 +45,17 @@ def _width(nx, N, L, size):
         pitch = (xb | 1) + 1
         return size * (Nm * (16 * pitch + 4) + 2 * NmP * (NcP + 1) + 2 * NcP * (NmP + 1)) + 16 * N + 1024
 
-    n = 1
-    while n == 1 or -(-nx // n) >= 32:
-        if lds(-(-nx // n)) <= LDS:
-            return -(-nx // n)
-        n = max(n + 1, -(-nx // 64))
-    return 0
+    xb, n = nx, -(-nx // 64)
+    while lds(xb) > LDS:
+        xb, n = -(-nx // n), n + 1
+        if xb < 32:
+            return 32 if nx >= 32 and lds(32) <= LDS else 0
+    return xb
 
 
 # nx, ny, nz, L, precision, cells of a block
-CASES = [(65, 19, 2, 4, "fp64", 33), (97, 16, 1, 4, "fp64", 33), (64, 5, 3, 4, "fp64", 32), (100, 33, 1, 4, "fp32", 50),
+CASES = [(65, 19, 2, 4, "fp64", 33), (97, 16, 1, 4, "fp64", 33), (64, 5, 3, 4, "fp64", 32), (71, 5, 2, 4, "fp64", 32),
+         (54, 18, 2, 4, "fp64", 32), (100, 33, 1, 4, "fp32", 50),
          (129, 17, 2, 5, "fp32", 43), (97, 3, 2, 5, "fp32", 49), (65, 50, 1, 5, "fp32", 33),
          (68, 33, 2, 3, "fp64", 34), (131, 9, 2, 2, "fp64", 44), (77, 20, 1, 3, "fp64", 39)]
 
