@@ -600,21 +600,27 @@ static void set_blocks(Plan &pl, int bk, int ny, int nz)
 // transposed sweeps that follow tile waves.  nwg: directions of all sources.
 //
 // One block (a direction is one workgroup of nz waves): while every wave of the
-// barrier coupling has a slot at four a SIMD its fewer steps win, up to 12 layers;
-// from 13 on tile waves split the layers over compute units, which wins in FP64,
-// and in FP32 once there are more directions than those.  Several blocks: only
-// on grids so short in x and z that a tile's skew is most of its steps.  Timed on
-// 449 random sizes (us an iteration, separate maps, barrier / tiles): FP64 44 x 50 x
-// 11 with 96 directions 86 / 100, 120 x 36 x 12 with 144 143 / 146, 52 x 21 x 13
-// with 48 76 / 75, 83 x 20 x 16 with 80 102 / 91; 384 and 960 directions: 19 x 9 x 4
-// 38 / 43, 37 x 12 x 12 0.58 of the barrier's; FP32 94 x 48 x 14 with 48 100 / 110,
-// 19 x 10 x 14 with 384 0.88 of it; 5 x 119 x 5 with 80 81 / 100, 40 x 97 x 10 with
-// 80 124 / 102.  The rule's choice is 1% behind the better of the three couplings
-// in the mean (tiles wherever nz > 8 or FP32 directions exceed the units: 5.6%).
+// barrier coupling has a slot at four a SIMD its fewer steps win, up to 12 layers,
+// but in FP64 for rows so long that filling and draining is little of a sweep, and
+// for more directions than units where at most two streams of tiles are swept.  From
+// 13 layers on tile waves split them over compute units, which wins in FP64, and in
+// FP32 once there are more directions than those.  Several blocks: only few
+// directions on grids so short in x and z that a tile's skew is most of its steps.
+// Timed on 449 random sizes and on the 900 solves of another draw (us an iteration,
+// separate maps, barrier / tiles): FP64 44 x 50 x 11 with 96 directions 86 / 100, 120 x
+// 36 x 12 with 144 143 / 146, 180 x 13 x 12 with 24 124 / 111, 27 x 50 x 11 with 384 135 /
+// 159, 36 x 24 x 11 with 384 0.85 of the barrier's, 52 x 21 x 13 with 48 76 /
+// 75, 83 x 20 x 16 with 80 102 / 91; 19 x 9 x 4 with 384 38 / 43, 37 x 12 x 12 with
+// 960 0.58 of the barrier's; FP32 94 x 48 x 14 with 48 100 / 110, 19 x 10 x 14 with
+// 384 0.88 of it; 5 x 119 x 5 with 80 81 / 100, 40 x 97 x 10 with 80 124 / 102.
 static bool barrier_first(int nx, int ny, int nz, long nwg, bool is64, int ncu)
 {
-    if (ny <= 64 && nz <= 16) return nwg * nz <= 16L * ncu && (nz <= 12 || (!is64 && nwg <= ncu));
-    return nz <= 8 && nx * nz <= 96;
+    if (ny <= 64 && nz <= 16) {
+        if (nwg * nz > 16L * ncu) return false;
+        if (nz <= 8) return true;
+        return nz <= 12 ? !is64 || (nx <= 6 * ny && (ny > 32 || nwg <= ncu)) : !is64 && nwg <= ncu;
+    }
+    return nz <= 8 && nx * nz <= 96 && nwg * nz <= 8L * ncu;
 }
 
 static int check_consistency(dct_ctx *ctx, const dct_opts &o, Plan &pl)
