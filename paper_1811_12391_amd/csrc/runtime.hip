@@ -1211,6 +1211,40 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
         return hipSuccess;
     };
 
+    // D map, combine and M map as one kernel (k_dcm): FP64 / FP32, a block's
+    // tile and the tables within the workgroup's LDS, the directions of a class
+    // within one round of loads, 32-bit offsets of one source's q, psi, ext and
+    // phi; by default when there are enough blocks to fill the GPU (one or two
+    // workgroups per CU at a time; measured: 36 sources FP64 220 against 302 ms,
+    // the 128 x 128 x 32 abdomen FP32 98 against 109 ms, FP64 184 us in
+    // x blocks against 290 for the three kernels)
+    cb.xb = mode <= 1 ? dcm_block(cb, ma, is64, ctx->lds_max) : 0;
+    const bool fuse_ok = cb.xb > 0 && std::max(pl.Nc[0], pl.Nc[1]) <= 48 &&
+                         (size_t)std::max(N, Nm) * C * ts < ((size_t)1 << 31);
+    const int nxb = cb.xb > 0 ? (nx + cb.xb - 1) / cb.xb : 0, nyb = (ny + 15) / 16;
+    const long nblocks = (long)nz * nyb * nxb * B;
+    // persistent workgroups: as many as fit the device at once
+    const int dcm_wg = (fuse_ok && 2 * (dcm_lds_bytes(cb, ma, is64, cb.xb) + 1024) <= ctx->lds_max ? 2 : 1) * ctx->ncu;
+    // blocks of a row have to win back the rows they take beyond their cells and
+    // the blocks' last round: the separate kernels move (2 N + 10 Nm) / (2 N + 2 Nm)
+    // times the bytes.  Timed on 240 random sizes, an iteration of the separate kernels
+    // / fused: FP64 0.96 - 1.09 below the line, mostly under 1 (S8 P1 282 x 16 x 7
+    // 0.96, S8 P4 64 x 80 x 27 0.98, S6 P3 94 x 18 x 25 with 8 sources 1.09), above it
+    // 0.99 - 1.44 (S8 P3 128 x 144 x 30 1.05, S6 P3 256 x 64 x 21 with 8 sources 1.44);
+    // FP32 1.05 - 1.55 above its line, and S8 P4 88 x 1 x 8 with 16 sources 0.81 below
+    bool pays = nblocks >= ctx->ncu;
+    if (pays && nxb > 1) {
+        const double rows = (nx + 15.0 * nxb) / nx * 16.0 * nyb / ny;
+        const double rounds = (double)((nblocks + dcm_wg - 1) / dcm_wg) * dcm_wg / nblocks;
+        pays = (N + 5.0 * Nm) / (N + Nm) >= (is64 ? 0.71 : 0.5) * rows * rounds;
+    }
+    const bool fused = fuse_ok && aam == 0 && (o.fuse_maps > 0 || (o.fuse_maps == 0 && pays));
+    // right-hand sides in two halves on two streams (below), where the coupling takes
+    // a part of them
+    const bool two_streams = !o.use_graph && fused && (o.rhs_streams == 2 ||
+                             (o.rhs_streams == 0 && (long)B * N >= 4L * ctx->ncu));
+    auto halves = [&](int cpl) { return two_streams && (((cpl == 4 || cpl == 5) && B >= 2) || (cpl >= 9 && B >= 4)); };
+
     // ---------------- sweep schedule: given, cached, or timed now
     // schedule = (z layers per workgroup, coupling, chain): coupling 1 = LDS
     // progress counters between the waves of a workgroup, 2 = one barrier per
@@ -1274,7 +1308,7 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
     {
         int bk = o.sweep_bk > 0 ? o.sweep_bk : 16;
         int cpl = o.sweep_sync > 0 ? o.sweep_sync
-                                   : (!free_sched || !tile_ok ? 1 : (barrier_first(nx, ny, nz, (long)B * N, is64, ctx->ncu) ? 2 : 4));
+                                   : (!free_sched || !tile_ok ? 1 : (barrier_first(nx, ny, nz, (long)B * N, is64, ctx->ncu) && !halves(4) ? 2 : 4));
         chainK = o.sweep_chain > 1 ? o.sweep_chain :
                  ((cpl >= 6 && cpl <= 8 && !chain_ks.empty()) ? chain_ks.back() : 1);
         rhsK = o.sweep_rhs_chain > 0 ? o.sweep_rhs_chain : std::min(B, 4);
@@ -1288,7 +1322,7 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
             const int ask_chain = o.sweep_chain < 0 ? DCT_MAXCHAIN + 1 : (o.sweep_chain > 1 ? o.sweep_chain : 0);
             int form = (o.sweep_bk * 11 + o.sweep_sync) * (DCT_MAXCHAIN + 2) + ask_chain;
             form = (form * (DCT_MAXRC + 1) + o.sweep_rhs_chain) * 2 + (o.test_inflow ? 1 : 0);
-            form = form * 64 + (tile_ok ? std::min(tile_zg, 63) : 0);
+            form = (form * 64 + (tile_ok ? std::min(tile_zg, 63) : 0)) * 2 + (two_streams ? 1 : 0);
             const dct_ctx::Tuned *hit = nullptr;
             for (const auto &t : ctx->tuned)
                 if (t.nx == nx && t.ny == ny && t.nz == nz && t.N == N && t.B == B && t.prec == o.precision &&
@@ -1379,6 +1413,11 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
                     dlog(3, "tuning candidate: z layers %d, coupling %d, chained directions %d, chained sources %d: "
                             "%.3f ms per sweep", cand.bk, cand.cpl, cand.K, cand.R, ms / 3.0);
                     tune_ms += ms * 4.0 / 3.0;
+                    // (sweeps that run beside the other half's fused kernel count less: 36
+                    // sources at 64 x 64 x 16 S6 gain 8% of a solve that way, half of it sweeps;
+                    // 18 x 48 x 6 S8 with 16 sources 3.7 ms on layered waves, 4.4 on the barrier
+                    // coupling, whose sweeps alone are shorter)
+                    if (halves(cand.cpl)) ms *= 0.85f;
                     if (ms < best) {
                         best = ms;
                         bk = cand.bk;
@@ -1424,34 +1463,6 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
         ctx->last_rhs = rhsK;
     }
 
-    // D map, combine and M map as one kernel (k_dcm): FP64 / FP32, a block's
-    // tile and the tables within the workgroup's LDS, the directions of a class
-    // within one round of loads, 32-bit offsets of one source's q, psi, ext and
-    // phi; by default when there are enough blocks to fill the GPU (one or two
-    // workgroups per CU at a time; measured: 36 sources FP64 220 against 302 ms,
-    // the 128 x 128 x 32 abdomen FP32 98 against 109 ms, FP64 184 us in
-    // x blocks against 290 for the three kernels)
-    cb.xb = mode <= 1 ? dcm_block(cb, ma, is64, ctx->lds_max) : 0;
-    const bool fuse_ok = cb.xb > 0 && std::max(pl.Nc[0], pl.Nc[1]) <= 48 &&
-                         (size_t)std::max(N, Nm) * C * ts < ((size_t)1 << 31);
-    const int nxb = cb.xb > 0 ? (nx + cb.xb - 1) / cb.xb : 0, nyb = (ny + 15) / 16;
-    const long nblocks = (long)nz * nyb * nxb * B;
-    // persistent workgroups: as many as fit the device at once
-    const int dcm_wg = (fuse_ok && 2 * (dcm_lds_bytes(cb, ma, is64, cb.xb) + 1024) <= ctx->lds_max ? 2 : 1) * ctx->ncu;
-    // blocks of a row have to win back the rows they take beyond their cells and
-    // the blocks' last round: the separate kernels move (2 N + 10 Nm) / (2 N + 2 Nm)
-    // times the bytes.  Timed on 240 random sizes, an iteration of the separate kernels
-    // / fused: FP64 0.96 - 1.09 below the line, mostly under 1 (S8 P1 282 x 16 x 7
-    // 0.96, S8 P4 64 x 80 x 27 0.98, S6 P3 94 x 18 x 25 with 8 sources 1.09), above it
-    // 0.99 - 1.44 (S8 P3 128 x 144 x 30 1.05, S6 P3 256 x 64 x 21 with 8 sources 1.44);
-    // FP32 1.05 - 1.55 above its line, and S8 P4 88 x 1 x 8 with 16 sources 0.81 below
-    bool pays = nblocks >= ctx->ncu;
-    if (pays && nxb > 1) {
-        const double rows = (nx + 15.0 * nxb) / nx * 16.0 * nyb / ny;
-        const double rounds = (double)((nblocks + dcm_wg - 1) / dcm_wg) * dcm_wg / nblocks;
-        pays = (N + 5.0 * Nm) / (N + Nm) >= (is64 ? 0.71 : 0.5) * rows * rounds;
-    }
-    const bool fused = fuse_ok && aam == 0 && (o.fuse_maps > 0 || (o.fuse_maps == 0 && pays));
     ma.first_only = fused ? 1 : 0;
     ctx->last_fused = fused;
     ctx->last_warm = warm;
@@ -1481,12 +1492,7 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
     // right-hand sides in two halves on two streams: one half's sweep (issue-
     // and latency-bound) runs beside the other half's fused kernel (memory-
     // bound); the halves share no data, so each keeps its own order
-    int nstreams = 1;
-    const bool lw_cpl = ctx->last_sync == 4 || ctx->last_sync == 5;
-    const bool rc_cpl = (ctx->last_sync == 9 || ctx->last_sync == 10) && sw.rhsK > 1;
-    if (!o.use_graph && fused && ((lw_cpl && B >= 2) || (rc_cpl && B >= 4)) &&
-        (o.rhs_streams == 2 || (o.rhs_streams == 0 && (long)B * N >= 4L * ctx->ncu)))
-        nstreams = 2;
+    const int nstreams = halves(ctx->last_sync) && (ctx->last_sync < 9 || sw.rhsK > 1) ? 2 : 1;
     ctx->last_streams = nstreams;
     dlog(2, "solve %dx%dx%d N=%d B=%d G=%d precision %d: z layers %d, coupling %d, chained directions %d, "
             "chained sources %d, fused maps %d, streams %d", nx, ny, nz, N, B, G, o.precision, pl.BK, ctx->last_sync,
