@@ -1259,8 +1259,9 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
     // z layers per wave (same conditions, class layouts)
     double tune_ms = 0.0;
     const bool layered_ok = ny <= 64 && nz <= 16;
-    // tile waves (coupling 4): any grid of up to 64 layers whose faces fit the
-    // LDS when the schedule is free, the layered waves' grids when asked for
+    // tile waves (coupling 4): any grid whose faces and waves fit a workgroup (up to
+    // 64 layers, more in z groups) when the schedule is free, the layered waves'
+    // grids when asked for
     const bool free_sched = o.sweep_bk == 0 && o.sweep_sync == 0 && o.sweep_chain <= 1;
     const bool tile_ok = tile.S > 0 && (free_sched || layered_ok) && !o.test_inflow;
     const int tile_layers = std::min(4 * tile.K, nz);   // z layers of a tile-wave workgroup
