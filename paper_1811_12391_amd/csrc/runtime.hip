@@ -600,27 +600,30 @@ static void set_blocks(Plan &pl, int bk, int ny, int nz)
 // transposed sweeps that follow tile waves.  nwg: directions of all sources.
 //
 // One block (a direction is one workgroup of nz waves): while every wave of the
-// barrier coupling has a slot at four a SIMD its fewer steps win, up to 12 layers,
-// but in FP64 for rows so long that filling and draining is little of a sweep, and
-// for more directions than units where at most two streams of tiles are swept.  From
-// 13 layers on tile waves split them over compute units, which wins in FP64, and in
-// FP32 once there are more directions than those.  Several blocks: only few
-// directions on grids so short in x and z that a tile's skew is most of its steps.
-// Timed on 449 random sizes and on the 900 solves of another draw (us an iteration,
-// separate maps, barrier / tiles): FP64 44 x 50 x 11 with 96 directions 86 / 100, 120 x
-// 36 x 12 with 144 143 / 146, 180 x 13 x 12 with 24 124 / 111, 27 x 50 x 11 with 384 135 /
-// 159, 36 x 24 x 11 with 384 0.85 of the barrier's, 52 x 21 x 13 with 48 76 /
-// 75, 83 x 20 x 16 with 80 102 / 91; 19 x 9 x 4 with 384 38 / 43, 37 x 12 x 12 with
-// 960 0.58 of the barrier's; FP32 94 x 48 x 14 with 48 100 / 110, 19 x 10 x 14 with
-// 384 0.88 of it; 5 x 119 x 5 with 80 81 / 100, 40 x 97 x 10 with 80 124 / 102.
+// barrier coupling has a slot at four a SIMD (seven with more than two tiles of rows,
+// or up to 5 layers in FP32) its fewer steps win, up to 12 layers, but in FP64 for rows so long that filling
+// and draining is little of a sweep, and for more directions than units where at
+// most two streams of tiles are swept.  From 13 layers on tile waves split them over
+// compute units, which wins in FP64, and in FP32 once there are more directions than
+// those.  Several blocks: only on grids so short in x and z that a tile's skew is
+// most of its steps, with more than 4 layers for few directions.
+// Timed on 449 random sizes, the choice behind the best coupling by 0.6% in the mean
+// (tile waves wherever nz > 8 or directions exceed units: 5.6%).  Barrier / tiles, us
+// an iteration with separate maps, directions in brackets: FP64 44 x 50 x 11 (96) 86 /
+// 100, 120 x 36 x 12 (144) 143 / 146, 180 x 13 x 12 (24) 124 / 111, 27 x 50 x 11 (384)
+// 135 / 159, 52 x 21 x 13 (48) 76 / 75, 83 x 20 x 16 (80) 102 / 91, 19 x 9 x 4 (384) 38 /
+// 43; FP32 94 x 48 x 14 (48) 100 / 110; 5 x 119 x 5 (80) 81 / 100, 40 x 97 x 10 (80) 124 /
+// 102.  Tiles over barrier: FP64 36 x 24 x 11 (384) 0.85, 37 x 12 x 12 (960) 0.58; FP32
+// 19 x 10 x 14 (384) 0.88, 18 x 34 x 5 (960) 1.18, 12 x 258 x 1 (640) 1.43.
 static bool barrier_first(int nx, int ny, int nz, long nwg, bool is64, int ncu)
 {
+    const long slots = (ny > 32 || (!is64 && nz <= 5) ? 28L : 16L) * ncu;
     if (ny <= 64 && nz <= 16) {
-        if (nwg * nz > 16L * ncu) return false;
+        if (nwg * nz > slots) return false;
         if (nz <= 8) return true;
         return nz <= 12 ? !is64 || (nx <= 6 * ny && (ny > 32 || nwg <= ncu)) : !is64 && nwg <= ncu;
     }
-    return nz <= 8 && nx * nz <= 96 && nwg * nz <= 8L * ncu;
+    return nz <= 8 && nx * nz <= 96 && nwg * nz <= (nz <= 4 ? slots : 8L * ncu);
 }
 
 static int check_consistency(dct_ctx *ctx, const dct_opts &o, Plan &pl)
@@ -1231,19 +1234,22 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
     // / fused: FP64 0.96 - 1.09 below the line, mostly under 1 (S8 P1 282 x 16 x 7
     // 0.96, S8 P4 64 x 80 x 27 0.98, S6 P3 94 x 18 x 25 with 8 sources 1.09), above it
     // 0.99 - 1.44 (S8 P3 128 x 144 x 30 1.05, S6 P3 256 x 64 x 21 with 8 sources 1.44);
-    // FP32 1.05 - 1.55 above its line, and S8 P4 88 x 1 x 8 with 16 sources 0.81 below
+    // FP32 1.05 - 1.55 above its line, and S8 P4 88 x 1 x 8 with 16 sources 0.81 below.
+    // Sources enough for two streams, which need the fused kernel, lower the FP64 line
+    // (93 x 18 x 11 S8 P4 with 20 sources 42.7 / 38.0 ms a solve)
+    const bool may_halve = !o.use_graph && B >= 2 && (o.rhs_streams == 2 ||
+                           (o.rhs_streams == 0 && (long)B * N >= 4L * ctx->ncu));
     bool pays = nblocks >= ctx->ncu;
     if (pays && nxb > 1) {
         const double rows = (nx + 15.0 * nxb) / nx * 16.0 * nyb / ny;
         const double rounds = (double)((nblocks + dcm_wg - 1) / dcm_wg) * dcm_wg / nblocks;
-        pays = (N + 5.0 * Nm) / (N + Nm) >= (is64 ? 0.71 : 0.5) * rows * rounds;
+        pays = (N + 5.0 * Nm) / (N + Nm) >= (is64 ? (may_halve ? 0.58 : 0.71) : 0.5) * rows * rounds;
     }
     const bool fused = fuse_ok && aam == 0 && (o.fuse_maps > 0 || (o.fuse_maps == 0 && pays));
     // right-hand sides in two halves on two streams (below), where the coupling takes
     // a part of them
-    const bool two_streams = !o.use_graph && fused && (o.rhs_streams == 2 ||
-                             (o.rhs_streams == 0 && (long)B * N >= 4L * ctx->ncu));
-    auto halves = [&](int cpl) { return two_streams && (((cpl == 4 || cpl == 5) && B >= 2) || (cpl >= 9 && B >= 4)); };
+    const bool two_streams = fused && may_halve;
+    auto halves = [&](int cpl) { return two_streams && (cpl == 4 || cpl == 5 || (cpl >= 9 && B >= 4)); };
 
     // ---------------- sweep schedule: given, cached, or timed now
     // schedule = (z layers per workgroup, coupling, chain): coupling 1 = LDS
@@ -1418,7 +1424,9 @@ extern "C" int dct_solve(dct_ctx *ctx, const dct_opts *opts, dct_stats *stats)
                     // sources at 64 x 64 x 16 S6 gain 8% of a solve that way, half of it sweeps;
                     // 18 x 48 x 6 S8 with 16 sources 3.7 ms on layered waves, 4.4 on the barrier
                     // coupling, whose sweeps alone are shorter)
-                    if (halves(cand.cpl)) ms *= 0.85f;
+                    // (FP32 tile waves a little more than layered ones: 24 sources at 64 x 64 x
+                    // 16 S6 255 - 263 us a sweep against 258 - 261, a solve 16.0 ms against 14.7)
+                    if (halves(cand.cpl)) ms *= cand.cpl == 4 && !is64 ? 0.875f : 0.85f;
                     if (ms < best) {
                         best = ms;
                         bk = cand.bk;
