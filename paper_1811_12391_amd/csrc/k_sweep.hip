@@ -1867,7 +1867,8 @@ hipError_t launch_sweep(SweepArgs a, int is_f64, hipStream_t s, unsigned seq)
         // operands prefetched 4 steps ahead: at 2 layers per wave that holds 69
         // VGPRs instead of 110 with 8 steps, so three workgroups fit a CU instead
         // of two, and the sweep of the 36-source scan runs 4% faster (332 against
-        // 346 us); 2 steps (49 VGPRs) and 6 (89) were slower
+        // 346 us on class layouts of whole rows of y; 351 us in tiles of 16 rows);
+        // 2 steps (49 VGPRs) and 6 (89) were slower
 #define DCT_LW(T, ZL, MD) hipLaunchKernelGGL((k_sweep_lw<T, ZL, 4, MD>), lgrid, lblock, 0, s, a)
         if (is_f64) {
             if (mode == 1) DCT_LW(double, 2, 1); else DCT_LW(double, 2, 0);
